@@ -147,3 +147,31 @@ def test_hand_tie_workloads():
     ]
     for w in cases:
         _compare(w, np.arange(w.n_cells))
+
+
+def _bounds_case(kind):
+    """Workloads at the edges of the planner's bounds: equal operators (every grouping
+    of the same stage sizes ties on the bias, so the communication load decides), more
+    than 8 microbatch counts (the wider tables), memory that only some or none of a
+    degree's groupings fit, fewer operators than degrees, odd node sizes and batches."""
+    rng = np.random.default_rng(11)
+    ty = [dict(speed=1.0, mem=80e9, bw_intra=300e9, bw_inter=25e9, gpus_per_node=8),
+          dict(speed=0.5, mem=30e9, bw_intra=64e9, bw_inter=12.5e9, gpus_per_node=6)]
+    L = dict(equal=16, wide=20, tight=24, few=3)[kind]
+    one = lambda v: [v] * L
+    j = dict(batch=192 if kind == "wide" else 128, t=list(rng.uniform(1e-3, 4e-3, L)), p=list(rng.uniform(5e7, 2e8, L)),
+             a=list(rng.uniform(2e7, 6e7, L)), x=list(rng.uniform(1e6, 4e6, L)), a2a=one(0.0))
+    if kind == "equal":
+        j.update(t=one(2e-3), p=one(1e8), a=one(3e7), x=one(2e6))
+    if kind == "tight":
+        j.update(p=list(rng.uniform(2e9, 9e9, L)), a=list(rng.uniform(2e8, 2e9, L)))
+    m = [1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 64] if kind == "wide" else [1, 2, 4, 8, 16, 32, 64]
+    return wl.from_lists([j], ty, [1, 2, 5, 12, 16, 31, 48], m, kappa=1.1)
+
+
+@pytest.mark.parametrize("kind", ["equal", "wide", "tight", "few"])
+def test_bounds_keep_every_choice(kind):
+    w = _bounds_case(kind)
+    _, want = _compare(w, np.arange(w.n_cells))
+    fits = np.isfinite(want["T"])
+    assert fits.any() and (kind != "tight" or not fits.all())
