@@ -434,20 +434,6 @@ Workspace workspace_layout(const arena_ctx* c, int blocks)
     return w;
 }
 
-// Some type has one contention factor for all its counts: the kernel then
-// shares every tensor-degree problem of a (job, type) across counts.
-bool kappa_shared(const arena_ctx* c)
-{
-    if (c->n_counts < 2) return false;
-    for (int g = 0; g < c->n_types; ++g) {
-        bool same = true;
-        for (int ci = 1; ci < c->n_counts && same; ++ci)
-            same = c->kappa[(size_t)g * c->n_counts + ci] == c->kappa[(size_t)g * c->n_counts];
-        if (same) return true;
-    }
-    return false;
-}
-
 arena_status compute_size(arena_ctx* c)
 {
     if (c->size_valid) return ARENA_OK;
@@ -791,7 +777,6 @@ arena::EstimateArgs estimate_args(const arena_ctx* c, const int32_t* d_off, cons
     // one block per resident slot (four per CU); each takes items from the queue
     A.n_blocks = estimate_blocks(c);
     A.pure_cuts = d_pcut;
-    A.share_tp = kappa_shared(c) ? 1 : 0;
     // ascending: the kernel bisects the microbatch counts for the memory limit
     std::vector<int32_t> ms(c->m_values);
     std::sort(ms.begin(), ms.end());

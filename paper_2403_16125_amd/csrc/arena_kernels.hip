@@ -5,13 +5,22 @@
 // device queue, heaviest first, until none is left.
 //   set-up   the job's layer tables, parameter/activation prefix sums and the
 //            pure-compute cost prefix are staged in LDS once;
-//   shared   stage-partition problems that do not depend on the GPU count
-//            (the pure-compute problem, and every tensor degree when the
-//            type has one contention factor for all counts) are solved once
-//            per block for the union of the degrees any count requests;
-//   cells    the waves then take GPU counts from an LDS work counter, solve
-//            the count-specific problems, price every plan and reduce to the
-//            cell's best plan.
+//   pure     the pure-compute stage-partition problem, which depends on
+//            neither the GPU count nor the contention, is solved once per item
+//            for the degrees any count requests;
+//   cells    the waves then take GPU counts from an LDS work counter, bound
+//            every plan's degree one per lane, solve the problems best bound
+//            first, price the plans that may win and reduce to the cell's best
+//            plan.
+// Measured on 16384 jobs x 8 types x 131 counts: bounding each tensor degree's
+// problem in a pass of its own (6 of 64 lanes busy, each bounded problem's
+// degrees again when it was taken), with the pure plans priced first, took
+// 111.4 ms; one pass per cell and one order over all its plans take 92.5 ms.
+// With one contention factor per type (4096 jobs of 128 layers x 6 types x 10
+// counts) solving every tensor degree's problem for every requested degree at
+// set-up, to share over the counts, took 6.07 ms; certifying a bottleneck when
+// a plan needs one takes 3.66 ms (3.54 ms when those are kept for the other
+// counts, but then the work done depends on which wave comes first).
 // Nothing here is a dense contraction, so no MFMA: the work is compares,
 // min/max and adds on the vector ALU; reductions use DPP row operations.
 //
@@ -23,6 +32,7 @@
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "arena_internal.h"
 
@@ -30,11 +40,13 @@ namespace arena {
 namespace {
 
 constexpr double kInf = __builtin_huge_val();
-constexpr int kSlotsShared = 10;   // 1 pure problem + up to 9 tensor-degree problems
 constexpr int kPad = 8;            // prefix arrays hold +inf past the last layer
 constexpr int kLevels = 7;         // successor tables: 2^7 > largest stage count - 1
 constexpr int kLevelStride = 132;  // bytes per successor table (>= kLmax + 1)
-constexpr int kMaxCand = 8;        // tensor degrees of one cell (divisors of a node size <= 31)
+constexpr int kMaxTp = 8;          // tensor degrees of one type (divisors of a node size <= 31)
+constexpr int kMaxDps = 240;       // data-parallel degrees of one job: divisors <= 1024 of a batch below
+                                   // 2^31 (233 at most, for 1,396,755,360)
+constexpr int kTargets = 64;       // plans' (pp, tp, dp) a wave bounds and orders at a time
 static_assert(kMaxPlans <= 256, "plan entries are packed below the key in 8 bits");
 constexpr int kCertMinDegree = 2;  // a bottleneck certificate is tried for degrees from here up
 constexpr int kHeadLayers = 2;     // leading layers whose own memory bounds every plan (lower bounds)
@@ -49,10 +61,8 @@ struct WaveLds {
     uint32_t planKey[kMaxPlans];  // pp << 12 | tp << 7 | m
     double bq[kMaxM];             // samples per microbatch of the admissible counts, ascending m
     int32_t mq[kMaxM];            // those microbatch counts
-    double lbnd[kLmax];           // lower bound of the iteration time, by pipeline degree - 1
-    uint8_t tq[64];               // a problem's requested degrees, compacted
-    double cand_lb[kMaxCand];     // the cell's tensor-degree problems: least lower bound of their plans
-    uint8_t cand_tp[kMaxCand];    //   and their tensor degree
+    uint32_t tkey[kTargets];      // the cell's targets (target_key) and lower bounds of their plans' times,
+    float tlb[kTargets];          //   rounded down (+inf: no split fits memory)
     uint8_t cutrow[kLmax];        // with cuts on: the cut row of the plan holding the best time
     double cut_T;                 //   that time (+inf: none yet)
     int32_t cut_tp, cut_pp;       //   and its degrees
@@ -65,7 +75,6 @@ struct WaveLds {
     };
 };
 
-template <int SLOTS>
 struct BlockLds {
     float t[kLmax];
     float x[kLmax];
@@ -73,23 +82,21 @@ struct BlockLds {
     double Pp[kLmax + 1];         // prefix of parameter bytes
     double Ap[kLmax + 1];         // prefix of activation bytes
     double Upure[kLmax + kPad];   // prefix of the pure-compute per-sample cost (+inf padded)
-    double Wtab[SLOTS][kLmax + 1];// bottleneck of each shared problem, by degree (slot 0, the
-                                  // pure-compute problem: every degree up to the layer count)
-    uint8_t mmax[kMaxDp];         // [dp-1]: largest listed m with dp*m dividing the batch, 0: none
-    uint8_t mcnt[kMaxDp];         // [dp-1]: how many listed m have dp*m dividing the batch
+    double Wpure[kLmax + 1];      // its bottleneck, by degree (the degrees some count requests)
+    uint32_t dps[kMaxDps];        // data-parallel degrees some listed m admits, largest first: dp, and the
+                                  // largest m with dp m dividing the batch from bit 16
+    unsigned long long group_ok[kMaxDp / 64];   // set-up: the admitted degrees, 64 candidates per ballot
     double p_layer_max;           // largest parameter bytes of one layer
     double x_layer_min;           // smallest boundary activation bytes of one layer
     double x_sum, q_sum;          // sums over the layers of x and of the all-to-all bytes
     double head_p[kHeadLayers];   // parameter and activation bytes of the leading layers, as prefix
     double head_a[kHeadLayers];   //   differences (0 past the layer count)
     float xwin[kLmax + 1];        // [pp]: least x bytes of a window of layers whose pure-compute cost
-    float qwin[kLmax + 1];        //   reaches Wtab[0][pp], and least all-to-all bytes (rounded down)
-    int32_t slot_tp[SLOTS];
-    int32_t slot_var[SLOTS];
-    int32_t n_slots;
+    float qwin[kLmax + 1];        //   reaches Wpure[pp], and least all-to-all bytes (rounded down)
+    uint8_t wanted[kLmax + 4];    // [pp]: some count of the item requests the degree
+    uint8_t tps[kMaxTp];          // the node size's divisors
+    int32_t n_tps, n_dps;
     int32_t next_cell;
-    int32_t uniform;              // one kappa for every count of this type
-    int32_t moe;
     unsigned long long pure_cached[2];   // bit pp-1: the block's cache row of the pure split of pp is current
     WaveLds w[kWavesPerBlock];
 };
@@ -292,29 +299,23 @@ __device__ void build_prefix_u(const float* t, const float* x, const float* q, d
     seq_prefix<OS, 2>(u[0], u[1], jb.L, lane, U, tmp, true);
 }
 
-__device__ __forceinline__ bool adm_ok(const uint8_t* mmax, int dp)
+// A target of a cell: pipeline degree pp (bits 0-7), tensor degree tp (8-12),
+// data-parallel degree dp (13-23) and the largest admissible microbatch count
+// (24-30); pp tp dp = n.
+__device__ __forceinline__ unsigned target_key(int pp, int tp, int dp, int m)
 {
-    return mmax[dp - 1] != 0;
+    return (unsigned)pp | ((unsigned)tp << 8) | ((unsigned)dp << 13) | ((unsigned)m << 24);
 }
+__device__ __forceinline__ int target_pp(unsigned k) { return (int)(k & 0xFFu); }
+__device__ __forceinline__ int target_tp(unsigned k) { return (int)((k >> 8) & 0x1Fu); }
+__device__ __forceinline__ int target_dp(unsigned k) { return (int)((k >> 13) & 0x7FFu); }
+__device__ __forceinline__ int target_m(unsigned k) { return (int)(k >> 24); }
 
-// Is pp a requested degree of problem (n, tp, variant), tp dividing n?  pp divides n/tp, is
-// at most the layer count, leaves an admissible data-parallel degree, and
-// meets the all-to-all condition of the variant (variant 1: the MoE job's
-// single-GPU-per-stage plan dp = tp = 1, which has no all-to-all).
-__device__ __forceinline__ bool target_ok(const uint8_t* adm, const JobCtx& jb, int n, int tp,
-                                          int variant, int pp)
+// Targets of the pure-compute problem (no communication in the layer costs):
+// tensor degree 1, and for jobs with all-to-all layers one GPU per stage.
+__device__ __forceinline__ bool target_pure(unsigned k, bool moe)
 {
-    const int qn = exact_quot(n, tp);
-    if (pp > jb.L || pp > qn) return false;
-    // qn / pp when pp divides qn (qn <= 1024: the float quotient is within 1e-3)
-    const int d = (int)rintf((float)qn * __builtin_amdgcn_rcpf((float)pp));
-    if (__umul24(d, pp) != qn) return false;
-    if (variant == 0) {
-        if (jb.moe && pp >= n) return false;
-    } else if (pp != n) {
-        return false;
-    }
-    return adm_ok(adm, d);
+    return target_tp(k) == 1 && (!moe || target_dp(k) == 1);
 }
 
 // Degrees as a 128-bit mask (bit pp-1), uniform across the wave.
@@ -1217,8 +1218,8 @@ __device__ Stages ext_cuts(const ExtCtx& E, const double* U, const double* Pp, c
 // window of the best time so far is not solved.  Plan slots, tallies and the
 // returned least time as price_target.  The cut row of the cell's winner is
 // rebuilt at the end of the cell.
-template <int SLOTS, int S>
-__device__ double price_exact(const BlockLds<SLOTS>& B, WaveLds& Wv, const double* U, int lane, int mv,
+template <int S>
+__device__ double price_exact(const BlockLds& B, WaveLds& Wv, const double* U, int lane, int mv,
                               const JobCtx& jb, const TypeDev& ty, const Cell& cell, int tp, int pp, double W,
                               int& np, double best, double tie_eps, bool prune)
 {
@@ -1304,15 +1305,15 @@ __device__ double price_exact(const BlockLds<SLOTS>& B, WaveLds& Wv, const doubl
 // tie window (tie_eps) of `best` or of a count priced here.  Returns the
 // least time of the plans priced that fit (+inf if none): a plan of the
 // cell, so an upper bound of the cell's best time.
-template <int SLOTS, int S, bool MEM, bool EXT = false>
-__device__ double price_target(BlockLds<SLOTS>& B, WaveLds& Wv, const double* U, int lane, int mv,
+template <int S, bool MEM, bool EXT = false>
+__device__ double price_target(BlockLds& B, WaveLds& Wv, const double* U, int lane, int mv,
                                const JobCtx& jb, const TypeDev& ty, const Cell& cell, int tp, int pp,
                                double W, int& np, bool keep_cuts, double* R, double best, double tie_eps,
                                bool prune, uint8_t* pcache = nullptr)
 {
-    if constexpr (EXT) return price_exact<SLOTS, S>(B, Wv, U, lane, mv, jb, ty, cell, tp, pp, W, np, best, tie_eps,
+    if constexpr (EXT) return price_exact<S>(B, Wv, U, lane, mv, jb, ty, cell, tp, pp, W, np, best, tie_eps,
                                                      prune);
-    // S = 1: the pure-compute problem (U = Upure, W = Wtab[0][pp]), whose
+    // S = 1: the pure-compute problem (U = Upure, W = Wpure[pp]), whose
     // splits the block keeps in pcache
     Stages sg;
     if constexpr (S == 1)
@@ -1453,25 +1454,44 @@ __device__ double price_target(BlockLds<SLOTS>& B, WaveLds& Wv, const double* U,
 }
 
 
-// What the lower bounds of one problem's plans share: its tensor degree, n /
-// tp, a lower bound of its summed per-sample layer costs, and the gradient
-// all-reduce seconds per parameter byte over the intra- and inter-node links
-// without the ring factor (kappa 2 / (tp B)).
+// Least value of the wave (every lane gets it): the minimum takes its DPP
+// operand directly, one instruction per step.
+__device__ __forceinline__ float wave_min_f32(float v)
+{
+    const int id = __float_as_int(__builtin_huge_valf());
+    auto step = [&](auto ctrl, auto rows) {
+        v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(v), decltype(ctrl)::value,
+                                                                decltype(rows)::value, 0xf, false)));
+    };
+    step(std::integral_constant<int, 0xB1>{}, std::integral_constant<int, 0xf>{});    // quad_perm 1,0,3,2
+    step(std::integral_constant<int, 0x4E>{}, std::integral_constant<int, 0xf>{});    // quad_perm 2,3,0,1
+    step(std::integral_constant<int, 0x124>{}, std::integral_constant<int, 0xf>{});   // row_ror 4
+    step(std::integral_constant<int, 0x128>{}, std::integral_constant<int, 0xf>{});   // row_ror 8
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast 15
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});   // row_bcast 31
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// What the lower bounds of a cell's plans share: the gradient all-reduce
+// seconds per parameter byte over the intra- and inter-node links without the
+// ring factor at tp = 1 (kappa 2 / B), the tensor-parallel seconds of all
+// layers and of one x byte (times (tp-1)/tp), and the all-to-all seconds of
+// all layers and of one all-to-all byte.
 struct BoundCtx {
-    int tp, qn;
-    double rtp;
-    double UL;
     double ar_intra, ar_inter;
-    double cx, cq;                // seconds per sample per x byte and per all-to-all byte of a layer
+    double ul_tp, cx;
+    double ul_a2a, cq;
 };
 
-// Lower bound of the iteration time of every plan of degree pp (any listed m)
-// of problem bc, or +inf when no split of the layers into pp stages fits
-// memory.  Bounded below without the cuts:
+// Lower bound of the iteration time of every plan of target `key` (any listed
+// m), or +inf when no split of the layers into pp stages fits memory; one
+// target per lane, so a cell's bounds are one pass however many tensor degrees
+// they span.  Bounded below without the cuts:
 //   W*(pp) >= UL / pp (the stages tile the layers), and the stage of the
 //   optimal split whose pure-compute cost is largest reaches Wpure(pp) (no
 //   split of pp stages does better), so it is a window of layers reaching
-//   Wpure(pp): W*(pp) >= Wpure(pp) / tp + cx xwin(pp) + cq qwin(pp);
+//   Wpure(pp): W*(pp) >= Wpure(pp) / tp + cx xwin(pp) + cq qwin(pp) (the pure
+//   problem's targets take its exact bottleneck);
 //   the p2p bytes over the pp-1 stage boundaries >= (pp-1) min_l x_l;
 //   the largest stage's parameters >= max(P / pp, max_l p_l).
 // Memory: besides the parameter bound, the stage holding layer l has at most
@@ -1483,89 +1503,35 @@ struct BoundCtx {
 // For fixed dp, T = Bg/dp W + Bg/(dp m) (fill - W) + AR falls as m grows
 // (fill >= W), so the largest admissible m gives the bound.  Reciprocals are
 // estimates; a relative margin of 1e-9 covers them and the rounding.
-template <int SLOTS>
-__device__ double target_bound(const BlockLds<SLOTS>& B, const JobCtx& jb, const TypeDev& ty, const Cell& cell,
-                               unsigned gpn_divs, BoundCtx bc, int pp)
+__device__ __forceinline__ double target_bound(const BlockLds& B, const JobCtx& jb, const TypeDev& ty,
+                                               const Cell& cell, const BoundCtx& bc, unsigned key)
 {
+    const int pp = target_pp(key), tp = target_tp(key), dp = target_dp(key), m = target_m(key);
+    const bool pure = target_pure(key, jb.moe);
     const double rpp = rcp_approx((double)pp);
-    const int dp = (int)rint((double)bc.qn * rpp);                     // exact: pp divides qn
-    const int m = B.mmax[dp - 1];
+    const double rtp = tp == 1 ? 1.0 : rcp_approx((double)tp);
+    const double cap = ty.mem * (double)tp;
     const double plb = fmax(B.Pp[jb.L] * rpp, B.p_layer_max);
-    if (4.0 * plb > ty.mem * (double)bc.tp * (1.0 + 1e-9)) return kInf;
     const double b = rint((double)jb.Bg * rcp_approx((double)(dp * m)));   // exact: dp m divides Bg
-    {
-        const double cap = ty.mem * (double)bc.tp;
-        bool over = false;
+    bool over = 4.0 * plb > cap * (1.0 + 1e-9);
 #pragma unroll
-        for (int l = 1; l <= kHeadLayers; ++l) {
-            const int r = pp - l + 1;
-            const int f = m < r ? m : (r > 1 ? r : 1);
-            over |= 4.0 * B.head_p[l - 1] + (double)f * b * B.head_a[l - 1] > cap;
-        }
-        if (over) return kInf;
+    for (int l = 1; l <= kHeadLayers; ++l) {
+        const int r = pp - l + 1;
+        const int f = m < r ? m : (r > 1 ? r : 1);
+        over |= 4.0 * B.head_p[l - 1] + (double)f * b * B.head_a[l - 1] > cap;
     }
-    const double Wlb = fmax(bc.UL * rpp, B.Wtab[0][pp] * bc.rtp + (bc.cx * (double)B.xwin[pp] +
-                                                                    bc.cq * (double)B.qwin[pp]));
-    const double fill = bc.UL + cell.c_p2p * ((double)(pp - 1) * B.x_layer_min);
-    const int grp = dp * bc.tp;
-    const double c_ar = (grp < 32 && ((gpn_divs >> grp) & 1u)) ? bc.ar_intra : bc.ar_inter;
+    // the layer costs sum to at least UL (the job's sums of x and of the
+    // all-to-all bytes in the cost formula; margin for the rounding)
+    const double ftp = (double)(tp - 1);
+    const double ULp = B.Upure[jb.L];
+    const double UL = pure ? ULp : ((ULp + ftp * bc.ul_tp) * rtp + bc.ul_a2a) * (1.0 - 1e-12);
+    double Wlb = B.Wpure[pp] * rtp;
+    if (!pure) Wlb += bc.cx * (ftp * rtp) * (double)B.xwin[pp] + bc.cq * (double)B.qwin[pp];
+    Wlb = fmax(UL * rpp, Wlb);
+    const double fill = UL + cell.c_p2p * ((double)(pp - 1) * B.x_layer_min);
+    const double c_ar = (tiles_node(ty, dp * tp) ? bc.ar_intra : bc.ar_inter) * rtp;
     const double ar = dp > 1 ? plb * (c_ar * ((double)(dp - 1) * rcp_approx((double)dp))) : 0.0;
-    return (b * fill + (double)(m - 1) * (b * Wlb) + ar) * (1.0 - 1e-9);
-}
-
-// Lower bounds of the degrees in `tm` into Wv.lbnd[pp - 1], one lane per
-// degree (a problem requests at most 32 degrees: the divisors of n / tp);
-// returns the least of them (+inf: no degree fits memory).
-template <int SLOTS>
-__device__ __forceinline__ double degree_bounds(const BlockLds<SLOTS>& B, WaveLds& Wv, const Mask& tm, int lane,
-                                                const JobCtx& jb, const TypeDev& ty, const Cell& cell,
-                                                unsigned gpn_divs, const BoundCtx& bc)
-{
-    const bool b0 = (tm.lo >> lane) & 1ull, b1 = (tm.hi >> lane) & 1ull;
-    const unsigned r0 = __builtin_amdgcn_mbcnt_hi((unsigned)(tm.lo >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((unsigned)tm.lo, 0u));
-    const unsigned r1 = (unsigned)__popcll(tm.lo) +
-                        __builtin_amdgcn_mbcnt_hi((unsigned)(tm.hi >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((unsigned)tm.hi, 0u));
-    if (b0 && r0 < 64u) Wv.tq[r0] = (uint8_t)(1 + lane);
-    if (b1 && r1 < 64u) Wv.tq[r1] = (uint8_t)(65 + lane);
-    wave_sync();
-    double lb = kInf;
-    if (lane < tm.count()) {
-        const int pp = Wv.tq[lane];
-        lb = target_bound(B, jb, ty, cell, gpn_divs, bc, pp);
-        Wv.lbnd[pp - 1] = lb;
-    }
-    wave_sync();
-    return wave_reduce1<OpMin>(lb);
-}
-
-// The bound context of the cell's problem of tensor degree tp; the pure-
-// compute problem (tp = 1 without all-to-all) takes its exact cost sum.
-__device__ __forceinline__ BoundCtx bound_ctx(const Cell& cell, int tp, double UL, double ar_intra1,
-                                              double ar_inter1, double cx1 = 0.0, double cq = 0.0)
-{
-    BoundCtx bc;
-    bc.tp = tp;
-    bc.qn = exact_quot(cell.n, tp);
-    bc.rtp = tp == 1 ? 1.0 : rcp_approx((double)tp);
-    bc.UL = UL;
-    bc.ar_intra = ar_intra1 * bc.rtp;
-    bc.ar_inter = ar_inter1 * bc.rtp;
-    bc.cx = cx1 * ((double)(tp - 1) * bc.rtp);
-    bc.cq = cq;
-    return bc;
-}
-
-// Slot of the shared problem (tp, variant), -1 if the cell solves its own.
-template <int SLOTS>
-__device__ __forceinline__ int find_slot(const BlockLds<SLOTS>& B, int n_slots, bool moe, int tp, int var)
-{
-    if (tp == 1 && (var == 1 || !moe)) return 0;
-    int slot = -1;
-    for (int s = 1; s < n_slots; ++s)
-        if (B.slot_tp[s] == tp && B.slot_var[s] == var) slot = s;
-    return slot;
+    return over ? kInf : (b * fill + (double)(m - 1) * (b * Wlb) + ar) * (1.0 - 1e-9);
 }
 
 // Inclusive prefix sum over the wave (row shifts, then row broadcasts): the
@@ -1581,14 +1547,13 @@ __device__ __forceinline__ double wave_incl_sum(double v)
     return v;
 }
 
-// For every degree pp <= L: the least x bytes and the least all-to-all bytes
+// For every wanted degree pp <= L: the least x bytes and the least all-to-all bytes
 // of a window of consecutive layers whose pure-compute cost (a difference of
-// Upure, as the recursion forms it) reaches Wtab[0][pp], rounded down with a
+// Upure, as the recursion forms it) reaches Wpure[pp], rounded down with a
 // relative margin for the sums' rounding.  The waves share the degrees; the
 // x and all-to-all prefixes sit in each wave's UD (x even, all-to-all odd).
-template <int SLOTS>
-__device__ void window_minima(BlockLds<SLOTS>& B, WaveLds& Wv, int lane, int wid, int L, const float* xg,
-                              const float* qg, bool moe)
+__device__ void window_minima(BlockLds& B, WaveLds& Wv, int lane, int wid, int L, const Mask& wanted,
+                              const float* xg, const float* qg, bool moe)
 {
     double* P = Wv.UD;
     const double x0 = lane < L ? (double)xg[lane] : 0.0, x1 = lane + 64 < L ? (double)xg[lane + 64] : 0.0;
@@ -1614,8 +1579,10 @@ __device__ void window_minima(BlockLds<SLOTS>& B, WaveLds& Wv, int lane, int wid
     // the bottlenecks fall as pp grows (a split refines into one more stage), so
     // a start's first reaching end does too: each search ends at the last one
     int end[2] = {L, L};
-    for (int pp = wid + 1; pp <= L; pp += kWavesPerBlock) {
-        const double th = B.Wtab[0][pp];
+    int seen = 0;                 // wanted degrees so far: the waves take them in turn
+    for (int pp = wanted.next(1); pp; pp = wanted.next(pp + 1)) {
+        if ((seen++ & (kWavesPerBlock - 1)) != wid) continue;
+        const double th = B.Wpure[pp];
         double bx = kInf, bq = kInf;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -1670,10 +1637,10 @@ __device__ __forceinline__ void block_tallies(const EstimateArgs& A, WaveLds& Wv
 // MEM: the memory-constrained partition rule (each wave has one more LDS
 // row for its recursion); EXT: the exact-T rule (that row holds its
 // suffix recursion).
-template <int SLOTS, bool MEM, bool EXT = false>
+template <bool MEM, bool EXT = false>
 __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, int item)
 {
-    __shared__ BlockLds<SLOTS> B;
+    __shared__ BlockLds B;
     // the wave index (wid) is taken once per launch, as a scalar; the lane
     // index (counted by mbcnt, not kept from the launch) passes through an
     // empty asm statement once per item, so nothing derived from it is hoisted
@@ -1702,7 +1669,6 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
 #pragma unroll
     for (int i = 0; i < kMaxM; ++i)
         if (lane == i && i < A.n_m) mv = A.m_values[i];
-    const unsigned gpn_divs = ty.divs;   // bit d: d divides the node size
 
     // ---- stage the job
     bool has_q = false;
@@ -1713,12 +1679,43 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         B.q[tid] = qv;
         has_q = qv > 0.0f;
     }
+    if (tid < kLmax + 4) B.wanted[tid] = 0;
+    // largest admissible microbatch count of each data-parallel degree.  Below
+    // 2^20 samples the quotients come from float reciprocals (relative error
+    // about 2^-23, so rounding gives the exact quotient of a divisor) and a
+    // product check decides divisibility; larger batches take integer remainders.
+    const bool small_batch = jb.Bg < (1 << 20);
+    int mm[kMaxDp / 256];
+#pragma unroll
+    for (int h = 0; h < kMaxDp / 256; ++h) {
+        const int dp = h * 256 + tid + 1;
+        mm[h] = 0;
+        if (small_batch) {
+            const int q = (int)rintf((float)jb.Bg * __builtin_amdgcn_rcpf((float)dp));
+            if (q * dp == jb.Bg) {
+                for (int i = 0; i < A.n_m; ++i) {
+                    const int m = A.m_values[i];
+                    const int r = (int)rintf((float)q * __builtin_amdgcn_rcpf((float)m));
+                    if (r * m == q) mm[h] = m > mm[h] ? m : mm[h];
+                }
+            }
+        } else {
+            for (int i = 0; i < A.n_m; ++i)
+                if (jb.Bg % (dp * A.m_values[i]) == 0) mm[h] = A.m_values[i] > mm[h] ? A.m_values[i] : mm[h];
+        }
+        const unsigned long long okm = __ballot(mm[h] != 0);
+        if (lane == 0) B.group_ok[h * kWavesPerBlock + wid] = okm;
+    }
     jb.moe = __syncthreads_or(has_q) != 0;
     if (wid == 0 || wid == 1) {
         const float* src = (wid == 0 ? A.p : A.a) + off;
         const double v0 = lane < jb.L ? (double)src[lane] : 0.0;
         const double v1 = lane + 64 < jb.L ? (double)src[lane + 64] : 0.0;
         seq_prefix<1, 2>(v0, v1, jb.L, lane, wid == 0 ? B.Pp : B.Ap, Wv.UD + 1, false);
+        if (lane < kHeadLayers) {
+            const double* pre = wid == 0 ? B.Pp : B.Ap;
+            (wid == 0 ? B.head_p : B.head_a)[lane] = lane < jb.L ? pre[lane + 1] - pre[lane] : 0.0;
+        }
         if (wid == 0) {
             const double pm = wave_reduce1<OpMax>(fmax(v0, v1));
             if (lane == 0) B.p_layer_max = pm;
@@ -1726,9 +1723,6 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
     } else if (wid == 2) {
         build_prefix_u<1>(B.t, B.x, B.q, B.Upure, Wv.UD + 1, lane, jb, ty, 1.0, 1, false);
     } else {
-        bool same = true;
-        for (int c = lane; c < A.n_counts; c += 64) same &= A.kappa[g * A.n_counts + c] == A.kappa[g * A.n_counts];
-        const bool uni = __ballot(!same) == 0ull;
         const double x0 = lane < jb.L ? (double)A.x[off + lane] : kInf;
         const double x1 = lane + 64 < jb.L ? (double)A.x[off + lane + 64] : kInf;
         const double xm = wave_reduce1<OpMin>(fmin(x0, x1));
@@ -1736,107 +1730,90 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
                                               (lane + 64 < jb.L ? (double)A.x[off + lane + 64] : 0.0));
         const double qs = wave_reduce1<OpSum>((lane < jb.L ? (double)A.q[off + lane] : 0.0) +
                                               (lane + 64 < jb.L ? (double)A.q[off + lane + 64] : 0.0));
+        // the type's tensor degrees
+        const bool td = lane < 32 && ((ty.divs >> lane) & 1u);
+        const unsigned tdm = (unsigned)__ballot(td);
+        if (td) B.tps[__popc(tdm & ((1u << lane) - 1u))] = (uint8_t)lane;
         if (lane == 0) {
+            B.n_tps = __popc(tdm);
             B.x_sum = xs;
             B.q_sum = qs;
-            B.uniform = uni ? 1 : 0;
             B.next_cell = 0;
-            B.moe = jb.moe ? 1 : 0;
             B.x_layer_min = xm;
             B.pure_cached[0] = 0ull;
             B.pure_cached[1] = 0ull;
         }
     }
-    // largest admissible microbatch count of each data-parallel degree.  Below
-    // 2^20 samples the quotients come from float reciprocals (relative error
-    // about 2^-23, so rounding gives the exact quotient of a divisor) and a
-    // product check decides divisibility; larger batches take integer remainders.
-    const bool small_batch = jb.Bg < (1 << 20);
-    for (int dp = tid + 1; dp <= kMaxDp; dp += 256) {
-        int mm = 0, mc = 0;
-        if (small_batch) {
-            const int q = (int)rintf((float)jb.Bg * __builtin_amdgcn_rcpf((float)dp));
-            if (q * dp == jb.Bg) {
-                for (int i = 0; i < A.n_m; ++i) {
-                    const int m = A.m_values[i];
-                    const int r = (int)rintf((float)q * __builtin_amdgcn_rcpf((float)m));
-                    if (r * m == q) {
-                        mm = m > mm ? m : mm;
-                        ++mc;
-                    }
-                }
-            }
-        } else {
-            for (int i = 0; i < A.n_m; ++i)
-                if (jb.Bg % (dp * A.m_values[i]) == 0) {
-                    mm = A.m_values[i] > mm ? A.m_values[i] : mm;
-                    ++mc;
-                }
+    // the admitted data-parallel degrees, largest first
+    {
+        int total = 0, before[kMaxDp / 256] = {};
+#pragma unroll
+        for (int k = 0; k < kMaxDp / 64; ++k) {
+            const int c = __popcll(B.group_ok[k]);
+#pragma unroll
+            for (int h = 0; h < kMaxDp / 256; ++h)
+                if (k < h * kWavesPerBlock + wid) before[h] += c;
+            total += c;
         }
-        B.mmax[dp - 1] = (uint8_t)mm;
-        B.mcnt[dp - 1] = (uint8_t)mc;
+#pragma unroll
+        for (int h = 0; h < kMaxDp / 256; ++h)
+            if (mm[h] != 0) {
+                const unsigned long long okm = B.group_ok[h * kWavesPerBlock + wid];
+                const int rank = before[h] + __builtin_amdgcn_mbcnt_hi((unsigned)(okm >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((unsigned)okm, 0u));
+                if (total - 1 - rank < kMaxDps)
+                    B.dps[total - 1 - rank] = (unsigned)(h * 256 + tid + 1) | ((unsigned)mm[h] << 16);
+            }
+        if (tid == 0) B.n_dps = total < kMaxDps ? total : kMaxDps;
     }
     __syncthreads();
-
-    // ---- shared problems: the pure-compute one (every degree up to L: its
-    // bottlenecks also bound the other problems'), and every tensor degree
-    // when the type's contention factor is the same for all counts
-    if (tid == 0) {
-        int ns = 0;
-        B.slot_tp[ns] = 1;
-        B.slot_var[ns] = jb.moe ? 1 : 0;
-        ++ns;
-        if (SLOTS > 1 && A.share_tp && B.uniform) {
-            for (int tp = 1; tp <= ty.gpn && ns < SLOTS; ++tp) {
-                if (ty.gpn % tp != 0 || (tp == 1 && !jb.moe)) continue;
-                B.slot_tp[ns] = tp;
-                B.slot_var[ns] = 0;
-                ++ns;
-            }
+    const int n_dps = B.n_dps;
+    const int n_pairs = B.n_tps * n_dps;
+    const float r_dps = __builtin_amdgcn_rcpf((float)n_dps);
+    // the pair's tensor and data-parallel degree (tensor degrees ascending, then
+    // data-parallel degrees descending, so a problem's pipeline degrees ascend);
+    // returns the pipeline degree with n GPUs, 0 when the pair gives none of at
+    // most L stages.  The quotients of integers up to 2^11 from float
+    // reciprocals are exact after the offset or the product test.
+    auto pair_degree = [&](int e, int n, int& tp, int& dp, int& m) -> int {
+        const int ti = (int)(((float)e + 0.5f) * r_dps);
+        tp = B.tps[ti];
+        const unsigned d = B.dps[e - ti * n_dps];
+        dp = (int)(d & 0xFFFFu);
+        m = (int)(d >> 16);
+        const int grp = tp * dp;
+        const int pp = (int)rintf((float)n * __builtin_amdgcn_rcpf((float)grp));
+        return __umul24(pp, grp) == (unsigned)n && pp <= jb.L ? pp : 0;
+    };
+    // the degrees some count of the item requests
+    {
+        const int total = A.n_counts * n_pairs;
+        for (int z = tid; z < total; z += 64 * kWavesPerBlock) {
+            const int c = z / n_pairs;
+            int tp, dp, m;
+            const int pp = pair_degree(z - c * n_pairs, A.counts[c], tp, dp, m);
+            if (pp > 0) B.wanted[pp] = 1;
         }
-        B.n_slots = ns;
-    }
-    __syncthreads();
-    const int n_slots = B.n_slots;
-    if (tid < kHeadLayers) {
-        B.head_p[tid] = tid < jb.L ? B.Pp[tid + 1] - B.Pp[tid] : 0.0;
-        B.head_a[tid] = tid < jb.L ? B.Ap[tid + 1] - B.Ap[tid] : 0.0;
     }
     if (wid == 0) tally(Wv, lane, kCells, (unsigned long long)A.n_counts);
+    __syncthreads();
 
-    for (int s = wid; s < n_slots; s += kWavesPerBlock) {
-        const int tp = B.slot_tp[s], var = B.slot_var[s];
-        Mask tm;
-        if (s == 0) {
-            tm = ballot_mask(1 + lane <= jb.L, 65 + lane <= jb.L);
-        } else {
-            bool ok0 = false, ok1 = false;
-            for (int c = 0; c < A.n_counts; ++c) {
-                const int n = A.counts[c];
-                if (n % tp != 0) continue;
-                ok0 |= target_ok(B.mmax, jb, n, tp, var, 1 + lane);
-                ok1 |= target_ok(B.mmax, jb, n, tp, var, 65 + lane);
-            }
-            tm = ballot_mask(ok0, ok1);
-        }
-        if (!tm.any()) continue;
-        if (s > 0) {
-            build_prefix_u<2>(B.t, B.x, B.q, Wv.UD, Wv.UD + 1, lane, jb, ty, (double)A.kappa[g * A.n_counts],
-                              tp, true);
-        } else {
-            for (int e = lane; e < kLmax + kPad; e += 64) Wv.UD[2 * e] = B.Upure[e];
-            wave_sync();
-        }
-        double* Wrow = B.Wtab[s];
-        solve_dp(Wv, jb.L, tm, lane, [&](int pp, double W, Mask m) {
-            if (lane == 0) Wrow[pp] = W;
+    // ---- the pure-compute problem (no communication in the layer costs):
+    // independent of the count and of the contention, its bottlenecks price its
+    // plans in every cell and bound the other problems'
+    const Mask wanted = ballot_mask(1 + lane <= jb.L && B.wanted[1 + lane], 65 + lane <= jb.L && B.wanted[65 + lane]);
+    if (wid == 0 && wanted.any()) {
+        for (int e = lane; e < kLmax + kPad; e += 64) Wv.UD[2 * e] = B.Upure[e];
+        wave_sync();
+        solve_dp(Wv, jb.L, wanted, lane, [&](int pp, double W, Mask m) {
+            if (lane == 0) B.Wpure[pp] = W;
             return m;
         });
         tally(Wv, lane, kProblems, 1);
         tally(Wv, lane, kAlgOps, 8ull * (unsigned)jb.L);
     }
     __syncthreads();
-    window_minima(B, Wv, lane, wid, jb.L, A.x + off, A.q + off, jb.moe);
+    window_minima(B, Wv, lane, wid, jb.L, wanted, A.x + off, A.q + off, jb.moe);
     __syncthreads();
 
     // ---- cells: take counts, largest first, from the block's work counter
@@ -1858,164 +1835,150 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         int np = 0;
         double best = kInf;          // time of a fitting plan priced so far: bounds the cell's best
         if (lane == 0) Wv.cut_T = kInf;
-        // per-cell pieces of the bounds: all-reduce seconds per byte (tp = 1),
-        // and the tensor-parallel and all-to-all parts of a problem's cost sum.
-        // Bounds only: their relative margins cover reciprocal estimates (the
-        // memory rule's kernel keeps the divisions, which measured faster there);
-        // a bandwidth of +inf (no such link) gives 0, as the division does
-        auto bdiv = [](double x, double y) {
-            if constexpr (MEM) return x / y;
-            else return y < kInf ? x * rcp_approx(y) : 0.0;
-        };
-        const double ar_intra1 = bdiv(cell.kappa * 2.0, ty.bw_intra);
-        const double ar_inter1 = bdiv(cell.kappa * 2.0, ty.bw_inter);
-        const double ul_tp = bdiv(cell.kappa * 8.0 * B.x_sum, ty.bw_intra);
-        const double ul_a2a = jb.moe ? bdiv(cell.kappa * B.q_sum, ty.bw_inter) : 0.0;
-        // per byte of a layer: tensor-parallel seconds (times (tp-1)/tp) and all-to-all seconds
-        const double cx1 = bdiv(cell.kappa * 8.0, ty.bw_intra);
-        const double cq1 = jb.moe ? bdiv(cell.kappa, ty.bw_inter) : 0.0;
 
-        // plans of the pure-compute problem first: their bottlenecks are shared
-        {
-            const int var = jb.moe ? 1 : 0;
-            const Mask tm = ballot_mask(target_ok(B.mmax, jb, cell.n, 1, var, 1 + lane),
-                                        target_ok(B.mmax, jb, cell.n, 1, var, 65 + lane));
-            if (tm.any()) {
-                // bounds with the exact bottleneck; a degree is priced unless its
-                // bound is past the tie window of the best plan so far
-                degree_bounds(B, Wv, tm, lane, jb, ty, cell, gpn_divs,
-                              bound_ctx(cell, 1, B.Upure[jb.L], ar_intra1, ar_inter1));
-                for (int pp = tm.next(1); pp; pp = tm.next(pp + 1)) {
-                    const double lbp = Wv.lbnd[pp - 1];
-                    if (A.prune && !(lbp < kInf && lbp <= best * (1.0 + A.tie_eps))) continue;
-                    best = fmin(best, price_target<SLOTS, 1, MEM, EXT>(B, Wv, B.Upure, lane, mv, jb, ty, cell, 1, pp,
-                                                                  B.Wtab[0][pp], np, A.cuts != nullptr, R, best,
-                                                                  A.tie_eps, A.prune != 0, pcache));
-                }
-            }
-        }
-        // the other problems, best first: every tensor degree's problem gets the
-        // least lower bound of its plans, then the problem of least bound is
-        // solved while that bound lies within the tie window of `best` (so the
-        // first problem solved is the most promising one and its plans tighten
-        // the window for the rest).  Within a problem a degree whose bound
-        // exceeds the window cannot hold the cell's plan and is skipped, and the
-        // recursion stops after the last degree still wanted.
-        const int tpmax = cell.n < ty.gpn ? cell.n : ty.gpn;
-        int ncand = 0;
-        for (int tp = 1; tp <= tpmax; ++tp) {
-            if (((gpn_divs >> tp) & 1u) == 0 || exact_quot(cell.n, tp) * tp != cell.n) continue;
-            if (tp == 1 && !jb.moe) continue;          // the pure-compute problem
-            const Mask tm = ballot_mask(target_ok(B.mmax, jb, cell.n, tp, 0, 1 + lane),
-                                        target_ok(B.mmax, jb, cell.n, tp, 0, 65 + lane));
-            if (!tm.any()) continue;
-            // the layer costs sum to at least this (the job's sums of x and of the
-            // all-to-all bytes in the cost formula; margin for the rounding)
-            const double rtp = tp == 1 ? 1.0 : rcp_approx((double)tp);
-            const double ULb = ((B.Upure[jb.L] + (double)(tp - 1) * ul_tp) * rtp + ul_a2a) * (1.0 - 1e-12);
-            const double lb = degree_bounds(B, Wv, tm, lane, jb, ty, cell, gpn_divs,
-                                            bound_ctx(cell, tp, ULb, ar_intra1, ar_inter1, cx1, cq1));
-            if (lane == 0) {
-                Wv.cand_tp[ncand] = (uint8_t)tp;
-                Wv.cand_lb[ncand] = lb;
-            }
-            ++ncand;
-        }
-        wave_sync();
-        unsigned solved = 0;           // bit c: candidate c has been taken
+        // The cell's targets (pp, tp, dp) are listed, bounded one per lane, and
+        // taken in order of their bounds: the target of least bound, while that
+        // lies within the tie window of `best`, has its problem's layer costs
+        // built and, with the other targets of that problem within the window
+        // (least bound first), its bottleneck certified and its plans priced;
+        // what a certificate leaves open goes to one recursion per problem.
+        // Each priced plan tightens the window.  A target whose bound exceeds
+        // the window can hold neither the cell's plan nor a tie.  More than
+        // kTargets targets (of a batch with many divisors) take several lists.
+        int e0 = 0, nt = 0;
         for (;;) {
-            int csel = -1;
-            double lsel = kInf;
-            for (int c = 0; c < ncand; ++c) {
-                const double v = Wv.cand_lb[c];
-                if (!((solved >> c) & 1u) && (csel < 0 || v < lsel)) {
-                    csel = c;
-                    lsel = v;
+            int tp = 0, dp = 0, m = 0, pp = 0;
+            if (e0 + lane < n_pairs) pp = pair_degree(e0 + lane, cell.n, tp, dp, m);
+            const unsigned long long okm = __ballot(pp > 0);
+            const int add = __popcll(okm);
+            if (e0 < n_pairs && nt + add <= kTargets) {
+                if (pp > 0)
+                    Wv.tkey[nt + __builtin_amdgcn_mbcnt_hi((unsigned)(okm >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo((unsigned)okm, 0u))] =
+                        target_key(pp, tp, dp, m);
+                nt += add;
+                e0 += 64;
+                if (e0 < n_pairs) continue;
+            }
+            if (nt == 0) break;
+            wave_sync();
+            // ---- the list's bounds.  Bounds only: their relative margins cover
+            // reciprocal estimates (a bandwidth of +inf, no such link, gives 0, as
+            // the division does)
+            if (lane < nt) {
+                auto bdiv = [](double x, double y) { return y < kInf ? x * rcp_approx(y) : 0.0; };
+                BoundCtx bc;
+                bc.ar_intra = bdiv(cell.kappa * 2.0, ty.bw_intra);
+                bc.ar_inter = bdiv(cell.kappa * 2.0, ty.bw_inter);
+                bc.ul_tp = bdiv(cell.kappa * 8.0 * B.x_sum, ty.bw_intra);
+                bc.cx = bdiv(cell.kappa * 8.0, ty.bw_intra);
+                bc.ul_a2a = jb.moe ? bdiv(cell.kappa * B.q_sum, ty.bw_inter) : 0.0;
+                bc.cq = jb.moe ? bdiv(cell.kappa, ty.bw_inter) : 0.0;
+                Wv.tlb[lane] = __double2float_rd(target_bound(B, jb, ty, cell, bc, Wv.tkey[lane]));
+            }
+            wave_sync();
+            // the targets of `of` whose bounds lie within the window
+            auto within = [&](unsigned long long of) -> unsigned long long {
+                const float lb = Wv.tlb[lane];
+                const float lim = __double2float_ru(best * (1.0 + A.tie_eps));
+                return A.prune ? of & __ballot(lb < __builtin_huge_valf() && lb <= lim) : of;
+            };
+            // the target of least bound among `of` (not empty)
+            auto least = [&](unsigned long long of) -> int {
+                const bool in = ((of >> lane) & 1ull) != 0ull;
+                const float lb = Wv.tlb[lane];
+                const float v = wave_min_f32(in ? lb : __builtin_huge_valf());
+                return (int)__builtin_ctzll(__ballot(in && !(lb > v)));
+            };
+            auto key_of = [&](int t) -> unsigned {
+                return (unsigned)__builtin_amdgcn_readfirstlane((int)Wv.tkey[t]);
+            };
+            unsigned long long left = nt < 64 ? (1ull << nt) - 1ull : ~0ull;
+            for (;;) {
+                left = within(left);
+                if (!left) break;
+                const int t0 = least(left);
+                const unsigned k0 = key_of(t0);
+                if (target_pure(k0, jb.moe)) {
+                    left &= ~(1ull << t0);
+                    const int pc = target_pp(k0);
+                    best = fmin(best, price_target<1, MEM, EXT>(B, Wv, B.Upure, lane, mv, jb, ty, cell, 1, pc,
+                                                                B.Wpure[pc], np, A.cuts != nullptr, R, best, A.tie_eps,
+                                                                A.prune != 0, pcache));
+                    continue;
                 }
-            }
-            if (csel < 0) break;
-            if (A.prune && !(lsel < kInf && lsel <= best * (1.0 + A.tie_eps))) break;
-            // the first problem taken, if it is the last one bounded above, still has
-            // its degrees' bounds in lbnd (tp ascending: the largest tp, whose
-            // problem is most often taken first on the full round, is bounded last)
-            const bool fresh = solved == 0u && csel == ncand - 1;
-            solved |= 1u << csel;
-            const int tp = Wv.cand_tp[csel];
-            Mask tm = ballot_mask(target_ok(B.mmax, jb, cell.n, tp, 0, 1 + lane),
-                                  target_ok(B.mmax, jb, cell.n, tp, 0, 65 + lane));
-            if (!fresh) {
-                const double rtp = tp == 1 ? 1.0 : rcp_approx((double)tp);
-                const double ULb = ((B.Upure[jb.L] + (double)(tp - 1) * ul_tp) * rtp + ul_a2a) * (1.0 - 1e-12);
-                degree_bounds(B, Wv, tm, lane, jb, ty, cell, gpn_divs,
-                              bound_ctx(cell, tp, ULb, ar_intra1, ar_inter1, cx1, cq1));
-            }
-            // kept: no bound yet (+inf: memory rules the degree out), or within the window
-            {
-                const double lb0 = Wv.lbnd[lane], lb1 = Wv.lbnd[lane + 64];
-                const double lim = best * (1.0 + A.tie_eps);
-                if (A.prune) tm = tm & ballot_mask(lb0 < kInf && lb0 <= lim, lb1 < kInf && lb1 <= lim);
-            }
-            if (!tm.any()) continue;
-            double u[2];
-            layer_costs(B.t, B.x, B.q, lane, jb, ty, cell.kappa, tp, true, u);
-            seq_prefix<2, 2>(u[0], u[1], jb.L, lane, Wv.UD, Wv.UD + 1, true);
-            tally(Wv, lane, kAlgOps, 8ull * (unsigned)jb.L);
-            const int slot = find_slot(B, n_slots, jb.moe, tp, 0);
-            if (slot > 0) {
-                for (int pp = tm.next(1); pp; pp = tm.next(pp + 1)) {
-                    const double lbp = Wv.lbnd[pp - 1];
-                    if (A.prune && !(lbp <= best * (1.0 + A.tie_eps))) continue;
-                    best = fmin(best, price_target<SLOTS, 2, MEM, EXT>(B, Wv, Wv.UD, lane, mv, jb, ty, cell, tp, pp,
-                                                                  B.Wtab[slot][pp], np, A.cuts != nullptr, R, best,
-                                                                  A.tie_eps, A.prune != 0));
+                const int tp0 = target_tp(k0);
+                unsigned long long grp;
+                {
+                    const unsigned k = Wv.tkey[lane];
+                    grp = left & __ballot(target_tp(k) == tp0 && !target_pure(k, jb.moe));
                 }
-            } else {
-                // prices degree pp at bottleneck W; returns the degrees still wanted
-                auto price_deg = [&](int pp, double W, Mask m) -> Mask {
-                    best = fmin(best, price_target<SLOTS, 2, MEM, EXT>(B, Wv, Wv.UD, lane, mv, jb, ty, cell, tp, pp, W,
-                                                                  np, A.cuts != nullptr, R, best, A.tie_eps,
-                                                                  A.prune != 0));
-                    const double lim = best * (1.0 + A.tie_eps);
-                    Mask rest = m;                       // degrees still to come
-                    if (pp <= 64) rest.lo &= ~(1ull << (pp - 1)); else rest.hi &= ~(1ull << (pp - 65));
-                    return A.prune ? rest & ballot_mask(Wv.lbnd[lane] <= lim, Wv.lbnd[lane + 64] <= lim) : rest;
-                };
-                // the largest requested degrees first: where a certificate gives the
-                // bottleneck, the recursion is spared their rows (not under the
-                // exact-T rule, whose pricing outweighs its few recursions: taken
-                // largest first it prices more plans than it saves rows)
-                if constexpr (!EXT) {
-                    for (int pc = tm.last(); pc >= kCertMinDegree; pc = tm.last()) {
-                        // the memory test of the degree's largest admissible count
-                        // (not under the memory rule, whose splits differ)
-                        const int dpc = exact_quot(cell.n, tp * pc);
-                        double wc;
+                left &= ~grp;
+                double u[2];
+                layer_costs(B.t, B.x, B.q, lane, jb, ty, cell.kappa, tp0, true, u);
+                seq_prefix<2, 2>(u[0], u[1], jb.L, lane, Wv.UD, Wv.UD + 1, true);
+                tally(Wv, lane, kAlgOps, 8ull * (unsigned)jb.L);
+                unsigned long long open = 0ull;       // targets left to the recursion
+                int deepest = 0;                      // their largest degree
+                for (int t = t0;;) {
+                    const unsigned k = key_of(t);
+                    const int pc = target_pp(k);
+                    grp &= ~(1ull << t);
+                    double wc = -1.0;
+                    // a certificate, unless the recursion passes the degree's row anyway
+                    // (not under the exact-T rule, whose pricing outweighs its few
+                    // recursions)
+                    if (!EXT && pc >= kCertMinDegree && pc > deepest) {
+                        const Stages sp = pure_split(B.Upure, B.Wpure[pc], B.pure_cached, Wv, pcache, lane, jb.L, pc);
                         if constexpr (MEM) {
-                            wc = certified_bottleneck<2>(
-                                pure_split(B.Upure, B.Wtab[0][pc], B.pure_cached, Wv, pcache, lane, jb.L, pc), Wv,
-                                lane, jb.L, pc);
+                            wc = certified_bottleneck<2>(sp, Wv, lane, jb.L, pc);
                         } else {
-                            const int mx = B.mmax[dpc - 1];
-                            const double bmx = rint((double)jb.Bg * rcp_approx((double)(dpc * mx)));   // exact
-                            wc = certified_bottleneck<kCertRounds, true>(
-                                pure_split(B.Upure, B.Wtab[0][pc], B.pure_cached, Wv, pcache, lane, jb.L, pc), Wv,
-                                lane, jb.L, pc, B.Pp, B.Ap, ty.mem * (double)tp, bmx, mx < pc ? mx : pc);
+                            // with the memory test of the degree's largest admissible count
+                            // (not under the memory rule, whose splits differ)
+                            const int mx = target_m(k);
+                            const double bmx = rint((double)jb.Bg * rcp_approx((double)(target_dp(k) * mx)));   // exact
+                            wc = certified_bottleneck<kCertRounds, true>(sp, Wv, lane, jb.L, pc, B.Pp, B.Ap,
+                                                                         ty.mem * (double)tp0, bmx, mx < pc ? mx : pc);
                         }
-                        if (wc == -2.0) {
-                            // no count fits: its plans are priced infeasible without the bottleneck
-                            tally(Wv, lane, kPlans, (unsigned long long)B.mcnt[dpc - 1]);
-                            if (pc <= 64) tm.lo &= ~(1ull << (pc - 1)); else tm.hi &= ~(1ull << (pc - 65));
-                            continue;
-                        }
-                        if (!(wc >= 0.0)) break;
-                        tm = price_deg(pc, wc, tm);
                     }
+                    if (wc >= 0.0) {
+                        best = fmin(best, price_target<2, MEM, EXT>(B, Wv, Wv.UD, lane, mv, jb, ty, cell, tp0, pc, wc,
+                                                                    np, A.cuts != nullptr, R, best, A.tie_eps,
+                                                                    A.prune != 0));
+                        grp = within(grp);
+                    } else if (wc == -2.0) {
+                        // no count fits: its plans are priced infeasible without the bottleneck
+                        const double dm = (double)(target_dp(k) * mv);
+                        const bool adm = mv > 0 && rint((double)jb.Bg * rcp_approx(dm)) * dm == (double)jb.Bg;
+                        tally(Wv, lane, kPlans, (unsigned long long)__popcll(__ballot(adm)));
+                    } else {
+                        open |= 1ull << t;
+                        deepest = pc > deepest ? pc : deepest;
+                    }
+                    if (!grp) break;
+                    t = least(grp);
                 }
-                if (tm.any()) {
-                    solve_dp(Wv, jb.L, tm, lane, price_deg);
-                    tally(Wv, lane, kProblems, 1);
-                }
+                open = within(open);
+                if (!open) continue;
+                // the degrees still wanted, one mask bit each
+                auto degrees = [&](unsigned long long of) -> Mask {
+                    Mask dm{0ull, 0ull};
+                    for (; of; of &= of - 1ull) {
+                        const int d = target_pp(key_of((int)__builtin_ctzll(of)));
+                        if (d <= 64) dm.lo |= 1ull << (d - 1); else dm.hi |= 1ull << (d - 65);
+                    }
+                    return dm;
+                };
+                solve_dp(Wv, jb.L, degrees(open), lane, [&](int pc, double W, Mask) -> Mask {
+                    best = fmin(best, price_target<2, MEM, EXT>(B, Wv, Wv.UD, lane, mv, jb, ty, cell, tp0, pc, W, np,
+                                                                A.cuts != nullptr, R, best, A.tie_eps, A.prune != 0));
+                    open = within(open & ~__ballot(target_pp(Wv.tkey[lane]) == pc));
+                    return degrees(open);
+                });
+                tally(Wv, lane, kProblems, 1);
             }
+            nt = 0;
+            if (e0 >= n_pairs) break;
         }
         wave_sync();
 
@@ -2072,19 +2035,14 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
                 row[e] = (e < pp - 1) ? Wv.cutrow[e] : (uint8_t)0xFF;
         } else if (A.cuts) {
             // re-derive the winner's bottleneck and cuts
-            const int var = (jb.moe && dp * tp == 1) ? 1 : 0;
-            const int slot = find_slot(B, n_slots, jb.moe, tp, var);
             const double* U = Wv.UD;
-            if (slot == 0) {
+            double W = 0.0;
+            if (tp == 1 && (!jb.moe || dp == 1)) {
                 for (int e = lane; e < kLmax + kPad; e += 64) Wv.UD[2 * e] = B.Upure[e];
                 wave_sync();
+                W = B.Wpure[pp];
             } else {
-                build_prefix_u<2>(B.t, B.x, B.q, Wv.UD, Wv.UD + 1, lane, jb, ty, cell.kappa, tp, var == 0);
-            }
-            double W = 0.0;
-            if (slot >= 0) {
-                W = B.Wtab[slot][pp];
-            } else {
+                build_prefix_u<2>(B.t, B.x, B.q, Wv.UD, Wv.UD + 1, lane, jb, ty, cell.kappa, tp, true);
                 Mask one;
                 one.lo = pp <= 64 ? (1ull << (pp - 1)) : 0ull;
                 one.hi = pp > 64 ? (1ull << (pp - 65)) : 0ull;
@@ -2169,48 +2127,45 @@ __device__ __forceinline__ int take_item(const EstimateArgs& A, int* slot, int w
     return item;
 }
 
-template <int SLOTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_kernel(EstimateArgs A)
 {
     __shared__ int slot;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    estimate_body<SLOTS, false>(A, wid, kZeroTallies);
+    estimate_body<false>(A, wid, kZeroTallies);
     for (int item = take_item(A, &slot, wid); item >= 0; item = take_item(A, &slot, wid)) {
-        estimate_body<SLOTS, false>(A, wid, item);
+        estimate_body<false>(A, wid, item);
         __syncthreads();
     }
-    estimate_body<SLOTS, false>(A, wid, kFlushTallies);
+    estimate_body<false>(A, wid, kFlushTallies);
 }
 
 // The exact-T rule: each plan's split minimises its iteration time.
-template <int SLOTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_ext_kernel(EstimateArgs A)
 {
     __shared__ int slot;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    estimate_body<SLOTS, false, true>(A, wid, kZeroTallies);
+    estimate_body<false, true>(A, wid, kZeroTallies);
     for (int item = take_item(A, &slot, wid); item >= 0; item = take_item(A, &slot, wid)) {
-        estimate_body<SLOTS, false, true>(A, wid, item);
+        estimate_body<false, true>(A, wid, item);
         __syncthreads();
     }
-    estimate_body<SLOTS, false, true>(A, wid, kFlushTallies);
+    estimate_body<false, true>(A, wid, kFlushTallies);
 }
 
 // The memory rule's out-of-line solve raises register use; its kernel still
 // aims at four waves per SIMD (its recursion row shares LDS with the cut
 // tables, so four blocks fit a CU) and spills the rest, which measured faster
 // than three or two waves with fewer spills.
-template <int SLOTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_mem_kernel(EstimateArgs A)
 {
     __shared__ int slot;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    estimate_body<SLOTS, true>(A, wid, kZeroTallies);
+    estimate_body<true>(A, wid, kZeroTallies);
     for (int item = take_item(A, &slot, wid); item >= 0; item = take_item(A, &slot, wid)) {
-        estimate_body<SLOTS, true>(A, wid, item);
+        estimate_body<true>(A, wid, item);
         __syncthreads();
     }
-    estimate_body<SLOTS, true>(A, wid, kFlushTallies);
+    estimate_body<true>(A, wid, kFlushTallies);
 }
 
 // ------------------------------------------------------------ interpolated communication latency
@@ -2249,6 +2204,7 @@ struct TabBlockLds {
     WaveLds w[kWavesPerBlock];
     double cW[kTabCache];             // bottleneck cache of the (job, type): bottlenecks
     uint32_t ckey[kTabCache];         //   and their keys (0 empty)
+    int16_t lbnd[kWavesPerBlock][kLmax];  // a group's members by degree - 1 (-1: none)
 };
 
 // Bottleneck cache.  With one kappa for all counts of a type, a plan's
@@ -2599,7 +2555,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         wave_sync();
         // price plan e0 of the buffer and the unpriced plans of its group (each
         // slot receives its time and the priced flag); returns the best time
-        // so far.  Wv.lbnd[d - 1] holds the member of degree d (-1: none).
+        // so far.  B.lbnd[wid][d - 1] holds the member of degree d (-1: none).
         auto price_group = [&](int e0, double best_in) -> double {
             const unsigned key0 = Wv.planKey[e0] & kTabKeyMask;
             const int pp0 = (int)(key0 >> 12);
@@ -2608,8 +2564,8 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
             const double bq0 = rint((double)jb.Bg / (double)(dp0 * (int)(key0 & 0x7Fu)));
             const bool fl0 = dp0 * tp0 > 1;
             const double lim0 = best_in * (1.0 + A.tie_eps);
-            Wv.lbnd[lane] = -1.0;
-            Wv.lbnd[lane + 64] = -1.0;
+            B.lbnd[wid][lane] = -1;
+            B.lbnd[wid][lane + 64] = -1;
             wave_sync();
             for (int e = lane; e < np; e += 64) {
                 const unsigned k = Wv.planKey[e];
@@ -2621,10 +2577,10 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
                 if ((dp * tp > 1) != fl0 || rint((double)jb.Bg / (double)(dp * (int)(k & 0x7Fu))) != bq0) continue;
                 const double lbe = Wv.planT[e];
                 if (e != e0 && A.prune && !(lbe < kInf && lbe <= lim0)) continue;
-                Wv.lbnd[pp - 1] = (double)e;      // degrees of a group are distinct
+                B.lbnd[wid][pp - 1] = (int16_t)e;      // degrees of a group are distinct
             }
             wave_sync();
-            const Mask tm = ballot_mask(Wv.lbnd[lane] >= 0.0, Wv.lbnd[lane + 64] >= 0.0);
+            const Mask tm = ballot_mask(B.lbnd[wid][lane] >= 0, B.lbnd[wid][lane + 64] >= 0);
             double c[2];
             tab_layer_costs(B, lane, jb, ty, K, cell.kappa, dp0, tp0, bq0, c);
             seq_prefix<2, 2>(c[0], c[1], jb.L, lane, Wv.UD, Wv.UD + 1, true);
@@ -2632,7 +2588,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
             double bst = best_in;
             // prices degree pp of the group at bottleneck W; returns the degrees still wanted
             auto price_deg = [&](int pp, double W, Mask mk) -> Mask {
-                const int e = (int)Wv.lbnd[pp - 1];
+                const int e = B.lbnd[wid][pp - 1];
                 const int dp = exact_quot(cell.n, tp0 * pp);
                 const int m = (int)(Wv.planKey[e] & 0x7Fu);
                 const Stages sg = canonical_stages<2>(Wv.UD, Wv.J, lane, jb.L, pp, W);
@@ -2651,7 +2607,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
                 // members whose bound now lies past the window are left to the
                 // main loop, which skips them
                 const double lim = bst * (1.0 + A.tie_eps);
-                const int ea = (int)Wv.lbnd[lane], eb = (int)Wv.lbnd[lane + 64];
+                const int ea = B.lbnd[wid][lane], eb = B.lbnd[wid][lane + 64];
                 const bool ka = ea >= 0 && Wv.planT[ea] <= lim;
                 const bool kb = eb >= 0 && Wv.planT[eb] <= lim;
                 return rest & ballot_mask(ka, kb);
@@ -2842,20 +2798,11 @@ hipError_t launch_estimate(const EstimateArgs& args, hipStream_t stream)
     if (args.tab_k > 0) {
         hipLaunchKernelGGL(estimate_tab_kernel, grid, block, 0, stream, args);
     } else if (args.exact_t) {
-        if (args.share_tp)
-            hipLaunchKernelGGL((estimate_ext_kernel<kSlotsShared>), grid, block, 0, stream, args);
-        else
-            hipLaunchKernelGGL((estimate_ext_kernel<1>), grid, block, 0, stream, args);
+        hipLaunchKernelGGL(estimate_ext_kernel, grid, block, 0, stream, args);
     } else if (args.mem_rule) {
-        if (args.share_tp)
-            hipLaunchKernelGGL((estimate_mem_kernel<kSlotsShared>), grid, block, 0, stream, args);
-        else
-            hipLaunchKernelGGL((estimate_mem_kernel<1>), grid, block, 0, stream, args);
+        hipLaunchKernelGGL(estimate_mem_kernel, grid, block, 0, stream, args);
     } else {
-        if (args.share_tp)
-            hipLaunchKernelGGL((estimate_kernel<kSlotsShared>), grid, block, 0, stream, args);
-        else
-            hipLaunchKernelGGL((estimate_kernel<1>), grid, block, 0, stream, args);
+        hipLaunchKernelGGL(estimate_kernel, grid, block, 0, stream, args);
     }
     return hipGetLastError();
 }

@@ -156,6 +156,41 @@ def test_edge_cases(oracle):
     assert pp.max() >= 64          # deep pipelines of the 128-layer job are exercised
 
 
+@pytest.mark.parametrize("rule", [arena.PARTITION_BALANCED, arena.PARTITION_MEMORY, arena.PARTITION_EXACT_T])
+@pytest.mark.parametrize("shared", [True, False])
+def test_many_targets_per_cell(oracle, rule, shared):
+    """Batches and node sizes with many divisors, so that a cell lists more plans'
+    degrees than one wave has lanes (several lists per cell), from one tensor degree
+    to eight, with one contention factor or one per count;
+    and a batch of 2^20 samples and more, whose divisors come from integer remainders."""
+    rng = np.random.default_rng(8)
+    L = 61 if rule != arena.PARTITION_EXACT_T else 22      # the exact-T oracle's cost grows fast with L
+    # memory that some plans of a cell fit and others do not
+    job = lambda batch: dict(t=list(rng.lognormal(-5, 0.6, L)), p=list(rng.uniform(1e8, 4e8, L)),
+                             a=list(rng.uniform(2e4, 6e4, L)), x=list(rng.uniform(1e3, 4e3, L)),
+                             a2a=[0.0 if i % 3 else 2e3 for i in range(L)], batch=batch)
+    types = [dict(speed=1.0, mem=12e9, bw_intra=300e9, bw_inter=25e9, gpus_per_node=30),
+             dict(speed=0.6, mem=40e9, bw_intra=64e9, bw_inter=12.5e9, gpus_per_node=24),
+             dict(speed=0.4, mem=60e9, bw_intra=32e9, bw_inter=12.5e9, gpus_per_node=1)]
+    counts = [1, 7, 60, 360, 720, 840, 1024]
+    kappa = 1.25 if shared else rng.uniform(1.0, 2.0, len(types) * len(counts))
+    w = wl.from_lists([job(720720), job(1 << 21)], types, counts, [1, 2], kappa=kappa)
+    targets = max(sum(1 for tp in range(1, 31) if 30 % tp == 0 and n % tp == 0 for pp in range(1, L + 1)
+                      if n // tp % pp == 0 and 720720 % (n // tp // pp) == 0) for n in counts)
+    assert targets > 64
+    ids = np.arange(w.n_cells)
+    est = arena.Estimator(w, with_cuts=True, rule=rule)
+    try:
+        est.estimate()
+        res, cnt, size = est.results(ids), est.counters(), est.space_size()
+    finally:
+        est.close()
+    _say(f"many targets: rule {rule} shared {shared}: {targets} targets, {size['max_plans_per_cell']} plans per cell")
+    rep = compare(w, res, ids, oracle, rule=rule)
+    _check(rep, "many targets")
+    assert cnt["plans"] + cnt["plans_skipped"] == size["plans"] and 0 < rep["infeasible"] < len(ids)
+
+
 GOLDEN = json.load(open(os.path.join(HERE, "golden", "cells_hand.json")))
 
 
