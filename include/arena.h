@@ -280,7 +280,8 @@ arena_status arena_estimate(arena_ctx* ctx, float* t_iter, float* thr, uint32_t*
  * is allocated, enqueued or written (the need is 4 (J+1) + 4 J + 40 T + 8 NC
  * + 4 T NC + 4 J T bytes plus the communication tables and about 2 KB, for J
  * jobs, T types and NC counts, plus 8448 bytes per estimate block: one block
- * per item up to four per compute unit, 8.3 MiB on 256 CUs).  The tables are
+ * per item up to four per compute unit, 8.3 MiB on 256 CUs; with fewer items
+ * than that more blocks share an item when the cap leaves room for them).  The tables are
  * checked first, before the device is asked for its CU count.  INVALID_ARG
  * for a negative value.  arena_estimate also returns OUT_OF_MEMORY when a
  * device allocation fails. */

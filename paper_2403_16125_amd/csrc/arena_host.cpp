@@ -405,10 +405,10 @@ struct Workspace {
 };
 
 // Blocks of an estimate launch: one per resident slot (four per CU), at most
-// one per item.
-int estimate_blocks(const arena_ctx* c)
+// one per item and part.
+int estimate_blocks(const arena_ctx* c, int parts)
 {
-    return std::min(c->n_jobs * c->n_types, 4 * std::max(c->n_cus, 1));
+    return (int)std::min((int64_t)c->n_jobs * c->n_types * parts, (int64_t)4 * std::max(c->n_cus, 1));
 }
 
 // blocks = 0: the tables only (what the host knows before it asks the device
@@ -750,12 +750,35 @@ arena_status check_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
     return ARENA_OK;
 }
 
+// Parts an item's counts are split into, each taken by a block of its own, when
+// the items alone leave resident block slots empty (1 otherwise, and when the
+// parts' split caches would not fit `limit` bytes of workspace; 0: no limit).
+// Every part repeats the item's set-up, so how far splitting pays depends on
+// what a cell costs beside it.  Long jobs, the exact-T rule and tables have
+// cells that recurse deep: parts down to one count per wave, four blocks per
+// CU.  2 jobs (one of 128 layers) x 8 types x 131 counts: 2067 us in 16 blocks,
+// 399 in 128, 268 in 256, 223 in 528; 4 jobs of the exact-T rule x 4 types x 35
+// counts: 12.4 ms in 16 blocks, 4.6 in 176.  Shorter jobs: parts of at least two
+// counts per wave, two blocks per CU (co-resident set-ups slow each other).  32
+// jobs of up to 96 layers x 4 types x 35 counts: 188 us in 128 blocks, 137 in
+// 512, 219 in 1024; 64 jobs of up to 48 layers x 3 types x 7 counts: 67 us in
+// 192 blocks, 95 in 384.
+int estimate_parts(const arena_ctx* c, size_t limit)
+{
+    const bool deep = c->max_layers > 96 || c->partition_rule == ARENA_PARTITION_EXACT_T || c->tab_k > 0;
+    const int64_t items = (int64_t)c->n_jobs * c->n_types, cus = std::max(c->n_cus, 1);
+    const int64_t waves = arena::kWavesPerBlock;
+    const int64_t most = deep ? (c->n_counts + waves - 1) / waves : c->n_counts / (2 * waves);
+    const int parts = (int)std::max<int64_t>(1, std::min(most, (deep ? 4 : 2) * cus / items));
+    return limit == 0 || workspace_layout(c, estimate_blocks(c, parts)).total <= limit ? parts : 1;
+}
+
 // Kernel arguments from the context, with the library-owned tables at the
 // given device addresses.
 arena::EstimateArgs estimate_args(const arena_ctx* c, const int32_t* d_off, const int32_t* d_batch,
                                   const TypeDev* d_types, const int32_t* d_counts, const float* d_kappa,
                                   const int32_t* d_items, const int32_t* d_corder, unsigned long long* d_queue,
-                                  const double* d_tab, uint8_t* d_pcut, unsigned long long* d_counters,
+                                  const double* d_tab, uint8_t* d_pcut, unsigned long long* d_counters, int parts,
                                   float* t_iter, float* thr, uint32_t* plan, uint8_t* cuts, int32_t cuts_stride)
 {
     arena::EstimateArgs A;
@@ -775,7 +798,8 @@ arena::EstimateArgs estimate_args(const arena_ctx* c, const int32_t* d_off, cons
     for (int q = 0; q <= arena::kQueues; ++q) A.queue_off[q] = c->h_qoff[q];
     A.n_items = c->n_jobs * c->n_types;
     // one block per resident slot (four per CU); each takes items from the queue
-    A.n_blocks = estimate_blocks(c);
+    A.n_parts = parts;
+    A.n_blocks = estimate_blocks(c, parts);
     A.pure_cuts = d_pcut;
     // ascending: the kernel bisects the microbatch counts for the memory limit
     std::vector<int32_t> ms(c->m_values);
@@ -825,13 +849,14 @@ arena_status arena_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
     if (c->n_cus == 0 &&
         (e = hipDeviceGetAttribute(&c->n_cus, hipDeviceAttributeMultiprocessorCount, c->device)))
         return hip_fail(c, e, "hipDeviceGetAttribute");
-    const Workspace ws = workspace_layout(c, estimate_blocks(c));
+    const int parts = estimate_parts(c, (size_t)c->ws_limit);
+    const Workspace ws = workspace_layout(c, estimate_blocks(c, parts));
     if (c->ws_limit > 0 && ws.total > (size_t)c->ws_limit)
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "estimate: needs %zu bytes of device workspace (limit %lld)",
                     ws.total, (long long)c->ws_limit);
     st = ensure_device(c, stream);
     if (st != ARENA_OK) return st;
-    if ((e = ensure_capacity(&c->d_pcut, &c->cap_pcut, (size_t)arena::kPureCutBytes * estimate_blocks(c))))
+    if ((e = ensure_capacity(&c->d_pcut, &c->cap_pcut, (size_t)arena::kPureCutBytes * estimate_blocks(c, parts))))
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "split caches: %s", hipGetErrorString(e));
     if (c->order_dirty && (st = upload_orders(c, stream)) != ARENA_OK) return st;
     if (c->tab_k > 0) {
@@ -847,7 +872,7 @@ arena_status arena_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
     }
     const arena::EstimateArgs A =
         estimate_args(c, c->d_off, c->d_batch, c->d_types, c->d_counts, c->d_kappa, c->d_item_order,
-                      c->d_count_order, c->d_queue, c->d_tab, c->d_pcut, c->d_counters, t_iter, thr, plan, cuts,
+                      c->d_count_order, c->d_queue, c->d_tab, c->d_pcut, c->d_counters, parts, t_iter, thr, plan, cuts,
                       cuts_stride);
     if ((e = arena::launch_zero_counters(c->d_counters, arena::kNumCounters, stream)) ||
         (e = arena::launch_zero_counters(c->d_queue, arena::kQueues, stream)))
@@ -879,7 +904,8 @@ arena_status arena_estimate_noalloc(arena_ctx* c, float* t_iter, float* thr, uin
     if (c->n_cus == 0 &&
         (e = hipDeviceGetAttribute(&c->n_cus, hipDeviceAttributeMultiprocessorCount, c->device)))
         return hip_fail(c, e, "hipDeviceGetAttribute");
-    const Workspace ws = workspace_layout(c, estimate_blocks(c));
+    const int parts = estimate_parts(c, arena::kNoallocScratchBytes);
+    const Workspace ws = workspace_layout(c, estimate_blocks(c, parts));
     if (ws.total > arena::kNoallocScratchBytes)
         return fail(c, ARENA_ERR_OUT_OF_MEMORY,
                     "estimate_noalloc: the bound workload needs %zu bytes of scratch (max %zu): "
@@ -931,7 +957,7 @@ arena_status arena_estimate_noalloc(arena_ctx* c, float* t_iter, float* thr, uin
         (e = hipMemcpyAsync(d_tab, c->tab.data(), sizeof(double) * c->tab.size(), hipMemcpyHostToDevice, stream)))
         return hip_fail(c, e, "comm table copy");
     const arena::EstimateArgs A = estimate_args(c, d_off, d_batch, d_types, d_counts, d_kappa, d_items, d_corder,
-                                                d_queue, d_tab, d_pcut, d_counters, t_iter, thr, plan, cuts,
+                                                d_queue, d_tab, d_pcut, d_counters, parts, t_iter, thr, plan, cuts,
                                                 cuts_stride);
     // zeroed by a kernel, not a memset node
     if ((e = arena::launch_zero_counters(d_counters, arena::kNumCounters, stream)) ||

@@ -13,6 +13,7 @@ constexpr int kMaxPlans = 256;      // plans per cell
 constexpr int kMaxM = 16;           // microbatch choices
 constexpr int kWavesPerBlock = 4;   // waves of one (job, type) block, each on its own cells
 constexpr int kMaxDp = 1024;        // largest data-parallel degree (counts are <= 1024)
+constexpr int kMaxCounts = 512;     // GPU counts of the grid
 constexpr int kMaxTabPoints = 16;   // samples per communication latency table
 constexpr int kExactTMaxLayers = 96; // layers per job under the exact-T rule
 constexpr int kQueues = 8;          // item queues, one per XCD (each XCD has its own L2)
@@ -48,6 +49,8 @@ struct EstimateArgs {
     unsigned long long* queue;    // [kQueues] next item of each queue (zeroed before each launch)
     int32_t queue_off[kQueues + 1];
     int32_t n_items;              // J * T
+    int32_t n_parts;              // blocks that share an item's counts (part p takes every n_parts-th, from the
+                                  // p-th largest); more than 1 when the items alone leave block slots empty
     int32_t n_blocks;             // resident blocks launched; each takes items until none is left
     uint8_t* pure_cuts;           // [n_blocks * kPureCutBytes] each block's cache of pure-compute splits
     const int32_t* count_order;   // [NC] count indices, largest count first

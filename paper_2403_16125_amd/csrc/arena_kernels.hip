@@ -61,8 +61,13 @@ struct WaveLds {
     uint32_t planKey[kMaxPlans];  // pp << 12 | tp << 7 | m
     double bq[kMaxM];             // samples per microbatch of the admissible counts, ascending m
     int32_t mq[kMaxM];            // those microbatch counts
-    uint32_t tkey[kTargets];      // the cell's targets (target_key) and lower bounds of their plans' times,
-    float tlb[kTargets];          //   rounded down (+inf: no split fits memory)
+    union {
+        struct {
+            uint32_t tkey[kTargets];  // the cell's targets (target_key) and lower bounds of their plans' times,
+            float tlb[kTargets];      //   rounded down (+inf: no split fits memory)
+        };
+        int16_t member[kLmax];    // tables kernel: a group's plans by degree - 1 (-1: none)
+    };
     uint8_t cutrow[kLmax];        // with cuts on: the cut row of the plan holding the best time
     double cut_T;                 //   that time (+inf: none yet)
     int32_t cut_tp, cut_pp;       //   and its degrees
@@ -95,6 +100,8 @@ struct BlockLds {
     float qwin[kLmax + 1];        //   reaches Wpure[pp], and least all-to-all bytes (rounded down)
     uint8_t wanted[kLmax + 4];    // [pp]: some count of the item requests the degree
     uint8_t tps[kMaxTp];          // the node size's divisors
+    uint16_t cnt_n[kMaxCounts];   // GPU counts, largest first, and their indices; kept for the whole launch
+    uint16_t cnt_i[kMaxCounts];
     int32_t n_tps, n_dps;
     int32_t next_cell;
     unsigned long long pure_cached[2];   // bit pp-1: the block's cache row of the pure split of pp is current
@@ -1634,11 +1641,28 @@ __device__ __forceinline__ void block_tallies(const EstimateArgs& A, WaveLds& Wv
     }
 }
 
+// The counts, largest first, and their indices into LDS, once per launch: the
+// set-up and every cell read them (the first take_item's barrier orders them).
+__device__ __forceinline__ void stage_counts(const EstimateArgs& A, uint16_t* cnt_n, uint16_t* cnt_i, int tid)
+{
+    for (int c = tid; c < A.n_counts; c += 64 * kWavesPerBlock) {
+        const int i = A.count_order[c];
+        cnt_i[c] = (uint16_t)i;
+        cnt_n[c] = (uint16_t)A.counts[i];
+    }
+}
+
+// Counts of one part of an item: every n_parts-th, from the part-th largest.
+__device__ __forceinline__ int part_counts(const EstimateArgs& A, int part)
+{
+    return (A.n_counts - part + A.n_parts - 1) / A.n_parts;
+}
+
 // MEM: the memory-constrained partition rule (each wave has one more LDS
 // row for its recursion); EXT: the exact-T rule (that row holds its
 // suffix recursion).
 template <bool MEM, bool EXT = false>
-__device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, int item)
+__device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, int item, int part = 0)
 {
     __shared__ BlockLds B;
     // the wave index (wid) is taken once per launch, as a scalar; the lane
@@ -1653,6 +1677,7 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
     WaveLds& Wv = B.w[wid];
     double* const R = MEM ? Wv.R : nullptr;
     if (item < 0) {
+        if (item == kZeroTallies) stage_counts(A, B.cnt_n, B.cnt_i, tid);
         block_tallies(A, Wv, lane, item);
         return;
     }
@@ -1785,17 +1810,19 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         const int pp = (int)rintf((float)n * __builtin_amdgcn_rcpf((float)grp));
         return __umul24(pp, grp) == (unsigned)n && pp <= jb.L ? pp : 0;
     };
-    // the degrees some count of the item requests
-    {
-        const int total = A.n_counts * n_pairs;
-        for (int z = tid; z < total; z += 64 * kWavesPerBlock) {
-            const int c = z / n_pairs;
-            int tp, dp, m;
-            const int pp = pair_degree(z - c * n_pairs, A.counts[c], tp, dp, m);
-            if (pp > 0) B.wanted[pp] = 1;
+    // the degrees some count of the item requests: a lane per pair, a wave per
+    // fourth count
+    for (int e = lane; e < n_pairs; e += 64) {
+        const int ti = (int)(((float)e + 0.5f) * r_dps);
+        const int grp = (int)B.tps[ti] * (int)(B.dps[e - ti * n_dps] & 0xFFFFu);
+        const float r_grp = __builtin_amdgcn_rcpf((float)grp);
+        for (int c = part + A.n_parts * wid; c < A.n_counts; c += A.n_parts * kWavesPerBlock) {
+            const int n = B.cnt_n[c];
+            const int pp = (int)rintf((float)n * r_grp);
+            if (__umul24(pp, grp) == (unsigned)n && pp <= jb.L) B.wanted[pp] = 1;
         }
     }
-    if (wid == 0) tally(Wv, lane, kCells, (unsigned long long)A.n_counts);
+    if (wid == 0) tally(Wv, lane, kCells, (unsigned long long)part_counts(A, part));
     __syncthreads();
 
     // ---- the pure-compute problem (no communication in the layer costs):
@@ -1824,11 +1851,11 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         __asm__ volatile("" : "=v"(lane) : "0"((int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))));
         int cix = 0;
         if (lane == 0) cix = atomicAdd(&B.next_cell, 1);
-        cix = __builtin_amdgcn_readfirstlane(cix);
+        cix = __builtin_amdgcn_readfirstlane(cix) * A.n_parts + part;
         if (cix >= A.n_counts) break;
-        const int ci = A.count_order[cix];
+        const int ci = B.cnt_i[cix];
         Cell cell;
-        cell.n = A.counts[ci];
+        cell.n = B.cnt_n[cix];
         cell.kappa = (double)A.kappa[g * A.n_counts + ci];
         cell.B_pp = link_bw(cell.n <= ty.gpn, ty);
         cell.c_p2p = cell.kappa * 2.0 / cell.B_pp;
@@ -2106,34 +2133,42 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
 // b mod 8), so the types of one job run on one XCD and its layer tables are
 // fetched into that XCD's L2 once.  A block whose queue is empty takes from
 // the next queues in turn, so the work still balances over every CU whatever
-// the items really cost.  Returns the item, or -1 once every queue is empty
+// the items really cost.  An item is taken n_parts times in a row, once per
+// part.  Returns the item (and its part), or -1 once every queue is empty
 // (every block then leaves).
-__device__ __forceinline__ int take_item(const EstimateArgs& A, int* slot, int wid)
+__device__ __forceinline__ int take_item(const EstimateArgs& A, int* slot, int wid, int& part)
 {
     if (wid == 0 && __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) == 0u) {
-        int item = -1;
+        int item = -1, pt = 0;
         for (int r = 0; r < kQueues && item < 0; ++r) {
             const int qi = (int)((blockIdx.x + r) % kQueues);
-            const unsigned long long len = (unsigned long long)(A.queue_off[qi + 1] - A.queue_off[qi]);
-            if (len == 0ull) continue;
+            const unsigned len = (unsigned)(A.queue_off[qi + 1] - A.queue_off[qi]) * (unsigned)A.n_parts;
+            if (len == 0u) continue;
             const unsigned long long q = atomicAdd(&A.queue[qi], 1ull);
-            if (q < len) item = A.item_order[A.queue_off[qi] + (int)q];
+            if (q < len) {
+                const unsigned at = (unsigned)q / (unsigned)A.n_parts;
+                pt = (int)((unsigned)q - at * (unsigned)A.n_parts);
+                item = A.item_order[A.queue_off[qi] + (int)at];
+            }
         }
-        *slot = item;
+        slot[0] = item;
+        slot[1] = pt;
     }
     __syncthreads();
-    const int item = *slot;
+    const int item = slot[0];
+    part = slot[1];
     __syncthreads();
     return item;
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_kernel(EstimateArgs A)
 {
-    __shared__ int slot;
+    __shared__ int slot[2];
+    int part;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     estimate_body<false>(A, wid, kZeroTallies);
-    for (int item = take_item(A, &slot, wid); item >= 0; item = take_item(A, &slot, wid)) {
-        estimate_body<false>(A, wid, item);
+    for (int item = take_item(A, slot, wid, part); item >= 0; item = take_item(A, slot, wid, part)) {
+        estimate_body<false>(A, wid, item, part);
         __syncthreads();
     }
     estimate_body<false>(A, wid, kFlushTallies);
@@ -2142,11 +2177,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // The exact-T rule: each plan's split minimises its iteration time.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_ext_kernel(EstimateArgs A)
 {
-    __shared__ int slot;
+    __shared__ int slot[2];
+    int part;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     estimate_body<false, true>(A, wid, kZeroTallies);
-    for (int item = take_item(A, &slot, wid); item >= 0; item = take_item(A, &slot, wid)) {
-        estimate_body<false, true>(A, wid, item);
+    for (int item = take_item(A, slot, wid, part); item >= 0; item = take_item(A, slot, wid, part)) {
+        estimate_body<false, true>(A, wid, item, part);
         __syncthreads();
     }
     estimate_body<false, true>(A, wid, kFlushTallies);
@@ -2158,11 +2194,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // than three or two waves with fewer spills.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_mem_kernel(EstimateArgs A)
 {
-    __shared__ int slot;
+    __shared__ int slot[2];
+    int part;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     estimate_body<true>(A, wid, kZeroTallies);
-    for (int item = take_item(A, &slot, wid); item >= 0; item = take_item(A, &slot, wid)) {
-        estimate_body<true>(A, wid, item);
+    for (int item = take_item(A, slot, wid, part); item >= 0; item = take_item(A, slot, wid, part)) {
+        estimate_body<true>(A, wid, item, part);
         __syncthreads();
     }
     estimate_body<true>(A, wid, kFlushTallies);
@@ -2194,6 +2231,8 @@ struct TabBlockLds {
     double lat[2][kMaxTabPoints];
     double p_layer_max;               // largest parameter bytes of one layer
     double x_layer_min;               // smallest boundary activation bytes of one layer
+    uint16_t cnt_n[kMaxCounts];       // GPU counts, largest first, and their indices; kept for the whole launch
+    uint16_t cnt_i[kMaxCounts];
     int32_t next_cell;
     int32_t share;                    // one kappa for all counts of the type: bottlenecks are shared
     double Upure[kLmax + kPad];       // prefix of the pure-compute per-sample cost (+inf padded)
@@ -2204,7 +2243,6 @@ struct TabBlockLds {
     WaveLds w[kWavesPerBlock];
     double cW[kTabCache];             // bottleneck cache of the (job, type): bottlenecks
     uint32_t ckey[kTabCache];         //   and their keys (0 empty)
-    int16_t lbnd[kWavesPerBlock][kLmax];  // a group's members by degree - 1 (-1: none)
 };
 
 // Bottleneck cache.  With one kappa for all counts of a type, a plan's
@@ -2431,7 +2469,7 @@ constexpr unsigned kTabKeyMask = kTabPriced - 1u;
 // with it): a group takes only members within the window and drops the
 // degrees the window excludes as it tightens.  Then the cell's choice as in
 // estimate_kernel.
-__device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid, int item)
+__device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid, int item, int part = 0)
 {
     __shared__ TabBlockLds B;
     // lane index counted per item and per cell (as in estimate_body)
@@ -2441,6 +2479,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
     const int tid = wid * 64 + lane;
     WaveLds& Wv = B.w[wid];
     if (item < 0) {
+        if (item == kZeroTallies) stage_counts(A, B.cnt_n, B.cnt_i, tid);
         block_tallies(A, Wv, lane, item);
         return;
     }
@@ -2508,7 +2547,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         }
     }
     if (tid == 0) B.next_cell = 0;
-    if (wid == 0) tally(Wv, lane, kCells, (unsigned long long)A.n_counts);
+    if (wid == 0) tally(Wv, lane, kCells, (unsigned long long)part_counts(A, part));
     __syncthreads();
     const bool share = B.share != 0;
 
@@ -2517,11 +2556,11 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         __asm__ volatile("" : "=v"(lane) : "0"((int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))));
         int cix = 0;
         if (lane == 0) cix = atomicAdd(&B.next_cell, 1);
-        cix = __builtin_amdgcn_readfirstlane(cix);
+        cix = __builtin_amdgcn_readfirstlane(cix) * A.n_parts + part;
         if (cix >= A.n_counts) break;
-        const int ci = A.count_order[cix];
+        const int ci = B.cnt_i[cix];
         Cell cell;
-        cell.n = A.counts[ci];
+        cell.n = B.cnt_n[cix];
         cell.kappa = (double)A.kappa[g * A.n_counts + ci];
         cell.B_pp = 0.0;
         cell.c_p2p = 0.0;
@@ -2555,7 +2594,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         wave_sync();
         // price plan e0 of the buffer and the unpriced plans of its group (each
         // slot receives its time and the priced flag); returns the best time
-        // so far.  B.lbnd[wid][d - 1] holds the member of degree d (-1: none).
+        // so far.  Wv.member[d - 1] holds the member of degree d (-1: none).
         auto price_group = [&](int e0, double best_in) -> double {
             const unsigned key0 = Wv.planKey[e0] & kTabKeyMask;
             const int pp0 = (int)(key0 >> 12);
@@ -2564,8 +2603,8 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
             const double bq0 = rint((double)jb.Bg / (double)(dp0 * (int)(key0 & 0x7Fu)));
             const bool fl0 = dp0 * tp0 > 1;
             const double lim0 = best_in * (1.0 + A.tie_eps);
-            B.lbnd[wid][lane] = -1;
-            B.lbnd[wid][lane + 64] = -1;
+            Wv.member[lane] = -1;
+            Wv.member[lane + 64] = -1;
             wave_sync();
             for (int e = lane; e < np; e += 64) {
                 const unsigned k = Wv.planKey[e];
@@ -2577,10 +2616,10 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
                 if ((dp * tp > 1) != fl0 || rint((double)jb.Bg / (double)(dp * (int)(k & 0x7Fu))) != bq0) continue;
                 const double lbe = Wv.planT[e];
                 if (e != e0 && A.prune && !(lbe < kInf && lbe <= lim0)) continue;
-                B.lbnd[wid][pp - 1] = (int16_t)e;      // degrees of a group are distinct
+                Wv.member[pp - 1] = (int16_t)e;      // degrees of a group are distinct
             }
             wave_sync();
-            const Mask tm = ballot_mask(B.lbnd[wid][lane] >= 0, B.lbnd[wid][lane + 64] >= 0);
+            const Mask tm = ballot_mask(Wv.member[lane] >= 0, Wv.member[lane + 64] >= 0);
             double c[2];
             tab_layer_costs(B, lane, jb, ty, K, cell.kappa, dp0, tp0, bq0, c);
             seq_prefix<2, 2>(c[0], c[1], jb.L, lane, Wv.UD, Wv.UD + 1, true);
@@ -2588,7 +2627,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
             double bst = best_in;
             // prices degree pp of the group at bottleneck W; returns the degrees still wanted
             auto price_deg = [&](int pp, double W, Mask mk) -> Mask {
-                const int e = B.lbnd[wid][pp - 1];
+                const int e = Wv.member[pp - 1];
                 const int dp = exact_quot(cell.n, tp0 * pp);
                 const int m = (int)(Wv.planKey[e] & 0x7Fu);
                 const Stages sg = canonical_stages<2>(Wv.UD, Wv.J, lane, jb.L, pp, W);
@@ -2607,7 +2646,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
                 // members whose bound now lies past the window are left to the
                 // main loop, which skips them
                 const double lim = bst * (1.0 + A.tie_eps);
-                const int ea = B.lbnd[wid][lane], eb = B.lbnd[wid][lane + 64];
+                const int ea = Wv.member[lane], eb = Wv.member[lane + 64];
                 const bool ka = ea >= 0 && Wv.planT[ea] <= lim;
                 const bool kb = eb >= 0 && Wv.planT[eb] <= lim;
                 return rest & ballot_mask(ka, kb);
@@ -2734,11 +2773,12 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_tab_kernel(EstimateArgs A)
 {
-    __shared__ int slot;
+    __shared__ int slot[2];
+    int part;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     estimate_tab_body(A, wid, kZeroTallies);
-    for (int item = take_item(A, &slot, wid); item >= 0; item = take_item(A, &slot, wid)) {
-        estimate_tab_body(A, wid, item);
+    for (int item = take_item(A, slot, wid, part); item >= 0; item = take_item(A, slot, wid, part)) {
+        estimate_tab_body(A, wid, item, part);
         __syncthreads();
     }
     estimate_tab_body(A, wid, kFlushTallies);

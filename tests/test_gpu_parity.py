@@ -360,3 +360,40 @@ def test_hand_tie_and_link_cells():
     res, _, _ = _run(w)
     assert (res["dp"][0], res["tp"][0], res["pp"][0], res["m"][0]) == (3, 1, 1, 1)
     assert res["t_iter"][0] == pytest.approx(5.0, rel=1e-6)
+
+
+@pytest.mark.parametrize("kind", ["balanced", "memory", "exact-t", "tables"])
+def test_few_items_split_over_blocks(kind):
+    """With few (job, type) items the counts of an item are shared by several blocks:
+    every cell and cut row is bitwise that of the same job among many (one block per
+    item), for count lists that do not divide evenly, and the workspace cap that only
+    one block per item fits is still accepted, with the same cells."""
+    rule = dict(memory=arena.PARTITION_MEMORY).get(kind, arena.PARTITION_BALANCED)
+    if kind == "exact-t":
+        rule = arena.PARTITION_EXACT_T
+        w = wl.trace(n_jobs=280)
+    else:
+        w = wl.full(n_jobs=160, rounds=1)
+    tables = wl.comm_tables(w) if kind == "tables" else None
+    pick = [3, 8, 11]
+
+    def run(v, limit=0):
+        est = arena.Estimator(v, with_cuts=True, rule=rule, comm_tables=tables)
+        try:
+            est.set_workspace_limit(limit)
+            est.estimate()
+            return est.results(), est.counters(), est.space_size()
+        finally:
+            est.close()
+
+    many, _, _ = run(w)
+    cells = w.n_types * w.n_counts
+    ids = np.concatenate([np.arange(j * cells, (j + 1) * cells) for j in pick])
+    sub = w.subset_jobs(pick)
+    # 3 jobs' tables and one block per item, with room for no more
+    limit = 8448 * len(pick) * w.n_types + (16 << 10)
+    for lim in (0, limit):
+        few, cnt, size = run(sub, lim)
+        for k in ("t_iter", "thr", "plan", "cuts"):
+            assert np.array_equal(few[k].view(np.uint8), many[k][ids].view(np.uint8)), (kind, lim, k)
+        assert cnt["cells"] == len(ids) and cnt["plans"] + cnt["plans_skipped"] == size["plans"]
