@@ -59,6 +59,11 @@ struct arena_ctx {
     // cached space size
     bool size_valid = false;
     arena_space_size size{};
+    // plans of the jobs' distinct (layers, batch), by type, while size_valid
+    struct TypePlans { int64_t sum; int32_t most; };   // over the counts: their sum and the most of one cell
+    std::vector<std::vector<TypePlans>> key_plans;
+    std::vector<int32_t> key_jobs, key_layers;          // how many jobs have the key, its layer count
+    std::vector<int32_t> job_key;                       // each job's key
 
     // device state
     bool dev_ready = false;
@@ -85,19 +90,22 @@ struct arena_ctx {
     uint8_t* d_pcut = nullptr;                  // the estimate blocks' caches of pure-compute splits
     size_t cap_pcut = 0;
     int n_cus = 0;
+    int32_t* h_jobs = nullptr;                  // pinned staging of the job tables and of the work order,
+    int32_t* h_order = nullptr;                 //   reused once the copies from them are done
+    size_t cap_hjobs = 0, cap_horder = 0;
+    hipEvent_t jobs_done = nullptr, order_done = nullptr;
     float* h_kappa[2] = {nullptr, nullptr};     // pinned staging, double-buffered
     hipEvent_t kappa_done[2] = {nullptr, nullptr};
     size_t cap_hkappa = 0;
     int kslot = 0;
 
-    // proxy planner: power-of-two multisets per (count, stage count), memory bandwidths
+    // proxy planner: power-of-two multisets per (count, stage count)
     bool msets_dirty = true;
     std::vector<unsigned long long> msets;
     std::vector<int32_t> mset_off;
     unsigned long long* d_msets = nullptr;
     int32_t* d_mset_off = nullptr;
-    double* d_hbm = nullptr;
-    size_t cap_msets = 0, cap_mset_off = 0, cap_hbm = 0;
+    size_t cap_msets = 0, cap_mset_off = 0;
 
     // scheduler: device copy of counts and capacity, staged through pinned memory
     int32_t* d_sched = nullptr;
@@ -128,24 +136,6 @@ arena_status hip_fail(arena_ctx* c, hipError_t e, const char* what)
 
 bool is_pos_finite_or_inf(float v) { return v > 0.0f && !std::isnan(v); }
 
-// Plans of one cell: tp | n, tp | node size, pp | n/tp, pp <= L, dp = n/(tp pp),
-// m listed with dp*m | Bg.
-int64_t plans_of_cell(int n, int gpn, int L, int Bg, const std::vector<int32_t>& ms)
-{
-    int64_t cnt = 0;
-    for (int tp = 1; tp <= n && tp <= gpn; ++tp) {
-        if (n % tp || gpn % tp) continue;
-        const int q = n / tp;
-        for (int pp = 1; pp <= q && pp <= L; ++pp) {
-            if (q % pp) continue;
-            const int dp = q / pp;
-            for (int m : ms)
-                if (Bg % (dp * m) == 0) ++cnt;
-        }
-    }
-    return cnt;
-}
-
 void free_device(arena_ctx* c)
 {
     (void)hipFree(c->d_off);
@@ -164,15 +154,13 @@ void free_device(arena_ctx* c)
     c->cap_pcut = 0;
     (void)hipFree(c->d_msets);
     (void)hipFree(c->d_mset_off);
-    (void)hipFree(c->d_hbm);
     (void)hipFree(c->d_tab);
     c->d_tab = nullptr;
     c->cap_tab = 0;
     c->tab_dirty = c->tab_k > 0;
     c->d_msets = nullptr;
     c->d_mset_off = nullptr;
-    c->d_hbm = nullptr;
-    c->cap_msets = c->cap_mset_off = c->cap_hbm = 0;
+    c->cap_msets = c->cap_mset_off = 0;
     c->msets_dirty = true;
     (void)hipFree(c->d_sched);
     (void)hipHostFree(c->h_sched);
@@ -184,6 +172,13 @@ void free_device(arena_ctx* c)
         (void)hipHostFree(c->h_kappa[i]);
         if (c->kappa_done[i]) (void)hipEventDestroy(c->kappa_done[i]);
     }
+    (void)hipHostFree(c->h_jobs);
+    (void)hipHostFree(c->h_order);
+    if (c->jobs_done) (void)hipEventDestroy(c->jobs_done);
+    if (c->order_done) (void)hipEventDestroy(c->order_done);
+    c->h_jobs = c->h_order = nullptr;
+    c->cap_hjobs = c->cap_horder = 0;
+    c->jobs_done = c->order_done = nullptr;
     c->d_off = c->d_batch = nullptr;
     c->d_types = nullptr;
     c->d_counts = nullptr;
@@ -224,7 +219,23 @@ hipError_t ensure_capacity(T** ptr, size_t* cap, size_t n)
     return e;
 }
 
-arena_status ensure_device(arena_ctx* c, hipStream_t stream)
+// A pinned staging buffer of at least n words that no copy still reads.
+hipError_t ensure_staging(int32_t** ptr, size_t* cap, hipEvent_t done, size_t n)
+{
+    hipError_t e = hipEventSynchronize(done);
+    if (e != hipSuccess || (*cap >= n && *ptr)) return e;
+    (void)hipHostFree(*ptr);
+    *ptr = nullptr;
+    *cap = 0;
+    e = hipHostMalloc((void**)ptr, sizeof(int32_t) * (n ? n : 1), 0);
+    if (e == hipSuccess) *cap = n;
+    return e;
+}
+
+// Device tables of the bindings, brought up to date on `stream`; a kappa
+// waiting to be uploaded is staged for the caller's kernel to copy (`kappa_up`,
+// its source, when asked) or copied.
+arena_status ensure_device(arena_ctx* c, hipStream_t stream, const float** kappa_up = nullptr)
 {
     hipError_t e;
     if (!c->dev_ready) {
@@ -236,9 +247,8 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream)
             return e == hipErrorOutOfMemory ? fail(c, ARENA_ERR_OUT_OF_MEMORY, "queue") : hip_fail(c, e, "hipMalloc");
         if ((e = hipDeviceGetAttribute(&c->n_cus, hipDeviceAttributeMultiprocessorCount, c->device)))
             return hip_fail(c, e, "hipDeviceGetAttribute");
-        for (int i = 0; i < 2; ++i)
-            if ((e = hipEventCreateWithFlags(&c->kappa_done[i], hipEventDisableTiming)))
-                return hip_fail(c, e, "hipEventCreate");
+        for (hipEvent_t* ev : {&c->kappa_done[0], &c->kappa_done[1], &c->jobs_done, &c->order_done})
+            if ((e = hipEventCreateWithFlags(ev, hipEventDisableTiming))) return hip_fail(c, e, "hipEventCreate");
         c->dev_ready = true;
     }
     if (c->jobs_dirty) {
@@ -246,11 +256,14 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream)
             return fail(c, ARENA_ERR_OUT_OF_MEMORY, "job tables: %s", hipGetErrorString(e));
         if ((e = ensure_capacity(&c->d_batch, &c->cap_batch, (size_t)c->n_jobs)))
             return fail(c, ARENA_ERR_OUT_OF_MEMORY, "job tables: %s", hipGetErrorString(e));
-        if ((e = hipMemcpyAsync(c->d_off, c->off.data(), sizeof(int32_t) * (c->n_jobs + 1),
-                                hipMemcpyHostToDevice, stream)) ||
-            (e = hipMemcpyAsync(c->d_batch, c->batch.data(), sizeof(int32_t) * c->n_jobs,
-                                hipMemcpyHostToDevice, stream)) ||
-            (e = hipStreamSynchronize(stream)))
+        const size_t no = (size_t)c->n_jobs + 1, nb = (size_t)c->n_jobs;
+        if ((e = ensure_staging(&c->h_jobs, &c->cap_hjobs, c->jobs_done, no + nb)))
+            return fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned job staging: %s", hipGetErrorString(e));
+        std::memcpy(c->h_jobs, c->off.data(), sizeof(int32_t) * no);
+        std::memcpy(c->h_jobs + no, c->batch.data(), sizeof(int32_t) * nb);
+        if ((e = hipMemcpyAsync(c->d_off, c->h_jobs, sizeof(int32_t) * no, hipMemcpyHostToDevice, stream)) ||
+            (e = hipMemcpyAsync(c->d_batch, c->h_jobs + no, sizeof(int32_t) * nb, hipMemcpyHostToDevice, stream)) ||
+            (e = hipEventRecord(c->jobs_done, stream)))
             return hip_fail(c, e, "job table upload");
         c->jobs_dirty = false;
     }
@@ -304,6 +317,10 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream)
         const int s = c->kslot;
         if ((e = hipEventSynchronize(c->kappa_done[s]))) return hip_fail(c, e, "kappa slot wait");
         std::memcpy(c->h_kappa[s], c->kappa.data(), sizeof(float) * nk);
+        if (kappa_up) {
+            *kappa_up = c->h_kappa[s];       // the launch copies it, then records kappa_done[kslot]
+            return ARENA_OK;
+        }
         if ((e = hipMemcpyAsync(c->d_kappa, c->h_kappa[s], sizeof(float) * nk,
                                 hipMemcpyHostToDevice, stream)) ||
             (e = hipEventRecord(c->kappa_done[s], stream)))
@@ -312,6 +329,82 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream)
         c->kappa_dirty = false;
     }
     return ARENA_OK;
+}
+
+// Size of the plan space, and the plans of each distinct (layers, batch) by
+// type.  The plans of a cell are the (tp, pp, dp, m) with tp pp dp = n, tp
+// dividing the node size, pp <= L and dp m dividing the batch: summed over the
+// divisors pp of n with the listed counts of every way to write n / pp as tp dp.
+void compute_size(arena_ctx* c)
+{
+    if (c->size_valid) return;
+    std::vector<std::vector<int32_t>> divisors((size_t)c->n_counts);
+    int top = 1;
+    for (int ci = 0; ci < c->n_counts; ++ci) {
+        const int n = c->counts[ci];
+        top = std::max(top, n);
+        for (int d = 1; d <= n; ++d)
+            if (n % d == 0) divisors[ci].push_back(d);
+    }
+    std::map<std::pair<int, int>, int> keys;
+    c->job_key.resize((size_t)c->n_jobs);
+    c->key_plans.clear();
+    c->key_jobs.clear();
+    c->key_layers.clear();
+    arena_space_size s{};
+    s.cells = (int64_t)c->n_jobs * c->n_types * c->n_counts;
+    s.max_layers = c->max_layers;
+    std::vector<int32_t> ways((size_t)top + 1);    // listed counts of the ways to split a product into tp dp
+    for (int j = 0; j < c->n_jobs; ++j) {
+        const int L = c->off[j + 1] - c->off[j], Bg = c->batch[j];
+        const auto ins = keys.emplace(std::make_pair(L, Bg), (int)c->key_plans.size());
+        c->job_key[j] = ins.first->second;
+        if (!ins.second) {
+            ++c->key_jobs[(size_t)ins.first->second];
+            continue;
+        }
+        std::vector<std::pair<int, int>> dps;      // dp, how many listed m have dp m dividing the batch
+        for (int dp = 1; dp <= top; ++dp) {
+            if (Bg % dp) continue;
+            int k = 0;
+            for (int m : c->m_values) k += Bg / dp % m == 0 ? 1 : 0;
+            if (k) dps.emplace_back(dp, k);
+        }
+        std::vector<arena_ctx::TypePlans> per((size_t)c->n_types, arena_ctx::TypePlans{0, 0});
+        for (int g = 0; g < c->n_types; ++g) {
+            int same = 0;                          // an earlier type with the same node size has the same plans
+            while (c->types[same].gpn != c->types[g].gpn) ++same;
+            if (same < g) {
+                per[g] = per[same];
+                continue;
+            }
+            std::fill(ways.begin(), ways.end(), 0);
+            for (int tp = 1; tp <= c->types[g].gpn; ++tp) {
+                if (c->types[g].gpn % tp) continue;
+                for (const auto& d : dps)
+                    if (tp * d.first <= top) ways[(size_t)tp * d.first] += d.second;
+            }
+            for (int ci = 0; ci < c->n_counts; ++ci) {
+                int32_t np = 0;
+                for (int pp : divisors[ci]) {
+                    if (pp > L) break;
+                    np += ways[(size_t)(c->counts[ci] / pp)];
+                }
+                per[g].sum += np;
+                per[g].most = std::max(per[g].most, np);
+            }
+        }
+        c->key_plans.push_back(std::move(per));
+        c->key_jobs.push_back(1);
+        c->key_layers.push_back(L);
+    }
+    for (size_t k = 0; k < c->key_plans.size(); ++k)
+        for (const auto& tp : c->key_plans[k]) {
+            s.plans += tp.sum * c->key_jobs[k];
+            s.max_plans_per_cell = std::max(s.max_plans_per_cell, tp.most);
+        }
+    c->size = s;
+    c->size_valid = true;
 }
 
 // Work order: jobs are dealt to the kernels' kQueues item queues (one per
@@ -323,32 +416,26 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream)
 void compute_orders(arena_ctx* c)
 {
     if (c->horder_valid) return;
+    compute_size(c);
     std::vector<int32_t>& corder = c->h_corder;
     corder.resize((size_t)c->n_counts);
     std::iota(corder.begin(), corder.end(), 0);
     std::stable_sort(corder.begin(), corder.end(),
                      [&](int a, int b) { return c->counts[a] > c->counts[b]; });
-    std::map<std::pair<int, int>, std::vector<double>> cost;
     const size_t items = (size_t)c->n_jobs * c->n_types;
-    std::vector<double> icost(items);
-    for (int j = 0; j < c->n_jobs; ++j) {
-        const int L = c->off[j + 1] - c->off[j];
-        auto key = std::make_pair(L, (int)c->batch[j]);
-        auto it = cost.find(key);
-        if (it == cost.end()) {
-            std::vector<double> per((size_t)c->n_types, 0.0);
-            for (int g = 0; g < c->n_types; ++g)
-                for (int ci = 0; ci < c->n_counts; ++ci)
-                    per[g] += (double)plans_of_cell(c->counts[ci], c->types[g].gpn, L, key.second,
-                                                    c->m_values) * (double)(L + 16);
-            it = cost.emplace(key, std::move(per)).first;
-        }
-        for (int g = 0; g < c->n_types; ++g) icost[(size_t)j * c->n_types + g] = it->second[g];
-    }
     const int T = c->n_types;
-    std::vector<double> jcost((size_t)c->n_jobs, 0.0);
-    for (int j = 0; j < c->n_jobs; ++j)
-        for (int g = 0; g < T; ++g) jcost[j] += icost[(size_t)j * T + g];
+    // a key's items: their costs and its types, heaviest first
+    std::vector<std::vector<int32_t>> key_types(c->key_plans.size(), std::vector<int32_t>((size_t)T));
+    std::vector<double> kcost(c->key_plans.size(), 0.0);
+    for (size_t k = 0; k < c->key_plans.size(); ++k) {
+        const auto& per = c->key_plans[k];
+        std::vector<int32_t>& types = key_types[k];
+        std::iota(types.begin(), types.end(), 0);
+        std::stable_sort(types.begin(), types.end(), [&](int a, int b) { return per[a].sum > per[b].sum; });
+        for (int g = 0; g < T; ++g) kcost[k] += (double)per[g].sum * (double)(c->key_layers[k] + 16);
+    }
+    std::vector<double> jcost((size_t)c->n_jobs);
+    for (int j = 0; j < c->n_jobs; ++j) jcost[j] = kcost[c->job_key[j]];
     std::vector<int32_t> jorder((size_t)c->n_jobs);
     std::iota(jorder.begin(), jorder.end(), 0);
     std::stable_sort(jorder.begin(), jorder.end(), [&](int a, int b) { return jcost[a] > jcost[b]; });
@@ -364,16 +451,10 @@ void compute_orders(arena_ctx* c)
     std::vector<int32_t>& iorder = c->h_iorder;
     iorder.clear();
     iorder.reserve(items);
-    std::vector<int32_t> types((size_t)T);
     for (int q = 0; q < arena::kQueues; ++q) {
         c->h_qoff[q] = (int32_t)iorder.size();
-        for (int j : qjobs[q]) {
-            std::iota(types.begin(), types.end(), 0);
-            std::stable_sort(types.begin(), types.end(), [&](int a, int b) {
-                return icost[(size_t)j * T + a] > icost[(size_t)j * T + b];
-            });
-            for (int g : types) iorder.push_back(j * T + g);
-        }
+        for (int j : qjobs[q])
+            for (int g : key_types[c->job_key[j]]) iorder.push_back(j * T + g);
     }
     c->h_qoff[arena::kQueues] = (int32_t)iorder.size();
     c->horder_valid = true;
@@ -387,11 +468,14 @@ arena_status upload_orders(arena_ctx* c, hipStream_t stream)
     if ((e = ensure_capacity(&c->d_item_order, &c->cap_items, items)) ||
         (e = ensure_capacity(&c->d_count_order, &c->cap_corder, (size_t)c->n_counts)))
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "work order: %s", hipGetErrorString(e));
-    if ((e = hipMemcpyAsync(c->d_item_order, c->h_iorder.data(), sizeof(int32_t) * items,
+    if ((e = ensure_staging(&c->h_order, &c->cap_horder, c->order_done, items + (size_t)c->n_counts)))
+        return fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned work order staging: %s", hipGetErrorString(e));
+    std::memcpy(c->h_order, c->h_iorder.data(), sizeof(int32_t) * items);
+    std::memcpy(c->h_order + items, c->h_corder.data(), sizeof(int32_t) * c->n_counts);
+    if ((e = hipMemcpyAsync(c->d_item_order, c->h_order, sizeof(int32_t) * items, hipMemcpyHostToDevice, stream)) ||
+        (e = hipMemcpyAsync(c->d_count_order, c->h_order + items, sizeof(int32_t) * c->n_counts,
                             hipMemcpyHostToDevice, stream)) ||
-        (e = hipMemcpyAsync(c->d_count_order, c->h_corder.data(), sizeof(int32_t) * c->n_counts,
-                            hipMemcpyHostToDevice, stream)) ||
-        (e = hipStreamSynchronize(stream)))
+        (e = hipEventRecord(c->order_done, stream)))
         return hip_fail(c, e, "work order upload");
     c->order_dirty = false;
     return ARENA_OK;
@@ -432,30 +516,6 @@ Workspace workspace_layout(const arena_ctx* c, int blocks)
     w.pcut = o;     o = up(o + (size_t)arena::kPureCutBytes * (size_t)blocks);
     w.total = o;
     return w;
-}
-
-arena_status compute_size(arena_ctx* c)
-{
-    if (c->size_valid) return ARENA_OK;
-    // plans depend on (L, Bg) only: group jobs
-    std::map<std::pair<int, int>, int64_t> groups;
-    for (int j = 0; j < c->n_jobs; ++j) ++groups[{c->off[j + 1] - c->off[j], c->batch[j]}];
-    arena_space_size s{};
-    s.cells = (int64_t)c->n_jobs * c->n_types * c->n_counts;
-    s.max_layers = c->max_layers;
-    for (const auto& kv : groups) {
-        for (int g = 0; g < c->n_types; ++g) {
-            for (int ci = 0; ci < c->n_counts; ++ci) {
-                int64_t np = plans_of_cell(c->counts[ci], c->types[g].gpn, kv.first.first,
-                                           kv.first.second, c->m_values);
-                s.plans += np * kv.second;
-                if (np > s.max_plans_per_cell) s.max_plans_per_cell = (int32_t)np;
-            }
-        }
-    }
-    c->size = s;
-    c->size_valid = true;
-    return ARENA_OK;
 }
 
 }  // namespace
@@ -754,18 +814,21 @@ arena_status check_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
 // the items alone leave resident block slots empty (1 otherwise, and when the
 // parts' split caches would not fit `limit` bytes of workspace; 0: no limit).
 // Every part repeats the item's set-up, so how far splitting pays depends on
-// what a cell costs beside it.  Long jobs, the exact-T rule and tables have
-// cells that recurse deep: parts down to one count per wave, four blocks per
-// CU.  2 jobs (one of 128 layers) x 8 types x 131 counts: 2067 us in 16 blocks,
-// 399 in 128, 268 in 256, 223 in 528; 4 jobs of the exact-T rule x 4 types x 35
-// counts: 12.4 ms in 16 blocks, 4.6 in 176.  Shorter jobs: parts of at least two
-// counts per wave, two blocks per CU (co-resident set-ups slow each other).  32
-// jobs of up to 96 layers x 4 types x 35 counts: 188 us in 128 blocks, 137 in
-// 512, 219 in 1024; 64 jobs of up to 48 layers x 3 types x 7 counts: 67 us in
-// 192 blocks, 95 in 384.
+// what a cell costs beside it.  The exact-T rule, tables, and long jobs over many
+// counts have cells that recurse deep: parts down to one count per wave, four
+// blocks per CU.  2 jobs (one of 128 layers) x 8 types x 131 counts: 2067 us in
+// 16 blocks, 399 in 128, 268 in 256, 223 in 528; 4 jobs of the exact-T rule x 4
+// types x 35 counts: 12.4 ms in 16 blocks, 4.6 in 176; 64 jobs with tables x 4
+// types x 11 counts: 576 us in 256 blocks, 417 in 768.  Otherwise: parts of at
+// least two counts per wave, two blocks per CU (co-resident set-ups slow each
+// other).  32 jobs of up to 96 layers x 4 types x 35 counts: 188 us in 128 blocks,
+// 137 in 512, 219 in 1024; 64 jobs of up to 48 layers x 3 types x 7 counts: 67 us
+// in 192 blocks, 95 in 384; 32 jobs of 128 layers x 4 types x 8 counts: 61 us in
+// 128 blocks, 85 in 384.
 int estimate_parts(const arena_ctx* c, size_t limit)
 {
-    const bool deep = c->max_layers > 96 || c->partition_rule == ARENA_PARTITION_EXACT_T || c->tab_k > 0;
+    const bool deep = c->partition_rule == ARENA_PARTITION_EXACT_T || (c->tab_k > 0 && c->n_counts > 8) ||
+                      (c->max_layers > 96 && c->n_counts >= 64);
     const int64_t items = (int64_t)c->n_jobs * c->n_types, cus = std::max(c->n_cus, 1);
     const int64_t waves = arena::kWavesPerBlock;
     const int64_t most = deep ? (c->n_counts + waves - 1) / waves : c->n_counts / (2 * waves);
@@ -776,7 +839,7 @@ int estimate_parts(const arena_ctx* c, size_t limit)
 // Kernel arguments from the context, with the library-owned tables at the
 // given device addresses.
 arena::EstimateArgs estimate_args(const arena_ctx* c, const int32_t* d_off, const int32_t* d_batch,
-                                  const TypeDev* d_types, const int32_t* d_counts, const float* d_kappa,
+                                  const TypeDev* d_types, const int32_t* d_counts, float* d_kappa,
                                   const int32_t* d_items, const int32_t* d_corder, unsigned long long* d_queue,
                                   const double* d_tab, uint8_t* d_pcut, unsigned long long* d_counters, int parts,
                                   float* t_iter, float* thr, uint32_t* plan, uint8_t* cuts, int32_t cuts_stride)
@@ -854,7 +917,8 @@ arena_status arena_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
     if (c->ws_limit > 0 && ws.total > (size_t)c->ws_limit)
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "estimate: needs %zu bytes of device workspace (limit %lld)",
                     ws.total, (long long)c->ws_limit);
-    st = ensure_device(c, stream);
+    const float* kappa_up = nullptr;
+    st = ensure_device(c, stream, &kappa_up);
     if (st != ARENA_OK) return st;
     if ((e = ensure_capacity(&c->d_pcut, &c->cap_pcut, (size_t)arena::kPureCutBytes * estimate_blocks(c, parts))))
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "split caches: %s", hipGetErrorString(e));
@@ -870,14 +934,17 @@ arena_status arena_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
             c->tab_dirty = false;
         }
     }
-    const arena::EstimateArgs A =
+    arena::EstimateArgs A =
         estimate_args(c, c->d_off, c->d_batch, c->d_types, c->d_counts, c->d_kappa, c->d_item_order,
                       c->d_count_order, c->d_queue, c->d_tab, c->d_pcut, c->d_counters, parts, t_iter, thr, plan, cuts,
                       cuts_stride);
-    if ((e = arena::launch_zero_counters(c->d_counters, arena::kNumCounters, stream)) ||
-        (e = arena::launch_zero_counters(c->d_queue, arena::kQueues, stream)))
-        return hip_fail(c, e, "counter reset");
+    A.kappa_src = kappa_up;
+    A.kappa_read = c->kappa_done[c->kslot];
     if ((e = arena::launch_estimate(A, stream))) return hip_fail(c, e, "estimate launch");
+    if (kappa_up) {
+        c->kslot ^= 1;
+        c->kappa_dirty = false;
+    }
     c->last_counters = c->d_counters;
     c->last_space_plans = c->size.plans;
     return ARENA_OK;
@@ -960,9 +1027,6 @@ arena_status arena_estimate_noalloc(arena_ctx* c, float* t_iter, float* thr, uin
                                                 d_queue, d_tab, d_pcut, d_counters, parts, t_iter, thr, plan, cuts,
                                                 cuts_stride);
     // zeroed by a kernel, not a memset node
-    if ((e = arena::launch_zero_counters(d_counters, arena::kNumCounters, stream)) ||
-        (e = arena::launch_zero_counters(d_queue, arena::kQueues, stream)))
-        return hip_fail(c, e, "counter reset");
     if ((e = arena::launch_estimate(A, stream))) return hip_fail(c, e, "estimate launch");
     c->last_counters = d_counters;
     c->last_space_plans = c->size.plans;
@@ -1059,7 +1123,7 @@ arena_status arena_proxy_estimate(arena_ctx* c, const arena_proxy_desc* d, float
         return fail(c, ARENA_ERR_INVALID_ARG, "proxy: n_ops=%d not in 1..%d", d->n_ops, ARENA_MAX_PROXY_OPS);
     if ((long long)c->n_jobs * c->n_types * c->n_counts > 0x7fffffffLL)
         return fail(c, ARENA_ERR_UNSUPPORTED, "proxy: more than 2^31-1 cells");
-    std::vector<double> hbm((size_t)c->n_types);
+    double hbm[ARENA_MAX_TYPES];
     for (int g = 0; g < c->n_types; ++g) {
         if (!(d->hbm_bw[g] > 0.0f) || !std::isfinite(d->hbm_bw[g]))
             return fail(c, ARENA_ERR_INVALID_ARG, "proxy: hbm_bw[%d] must be finite and > 0", g);
@@ -1084,19 +1148,13 @@ arena_status arena_proxy_estimate(arena_ctx* c, const arena_proxy_desc* d, float
             return hip_fail(c, e, "proxy table upload");
         c->msets_dirty = false;
     }
-    if ((e = ensure_capacity(&c->d_hbm, &c->cap_hbm, hbm.size())))
-        return fail(c, ARENA_ERR_OUT_OF_MEMORY, "proxy bandwidths: %s", hipGetErrorString(e));
-    if ((e = hipMemcpyAsync(c->d_hbm, hbm.data(), sizeof(double) * hbm.size(), hipMemcpyHostToDevice, stream)) ||
-        (e = hipStreamSynchronize(stream)))
-        return hip_fail(c, e, "proxy bandwidth upload");
-
     arena::ProxyArgs A;
     std::memset(&A, 0, sizeof(A));
     A.layer_offset = c->d_off;
     A.batch = c->d_batch;
     A.t = c->t; A.p = c->p; A.a = c->a; A.x = c->x; A.q = c->q;
     A.types = c->d_types;
-    A.hbm = c->d_hbm;
+    for (int g = 0; g < c->n_types; ++g) A.hbm[g] = hbm[g];
     A.counts = c->d_counts;
     A.kappa = c->d_kappa;
     A.msets = c->d_msets;

@@ -14,6 +14,7 @@ constexpr int kMaxM = 16;           // microbatch choices
 constexpr int kWavesPerBlock = 4;   // waves of one (job, type) block, each on its own cells
 constexpr int kMaxDp = 1024;        // largest data-parallel degree (counts are <= 1024)
 constexpr int kMaxCounts = 512;     // GPU counts of the grid
+constexpr int kMaxTypes = 64;       // GPU types
 constexpr int kMaxTabPoints = 16;   // samples per communication latency table
 constexpr int kExactTMaxLayers = 96; // layers per job under the exact-T rule
 constexpr int kQueues = 8;          // item queues, one per XCD (each XCD has its own L2)
@@ -44,9 +45,11 @@ struct EstimateArgs {
     const float* q;               // all-to-all bytes per sample
     const TypeDev* types;         // [T]
     const int32_t* counts;        // [NC]
-    const float* kappa;           // [T*NC]
+    float* kappa;                 // [T*NC]
+    const float* kappa_src;       // pinned host source the launch copies kappa from first, or null
+    hipEvent_t kappa_read;        // recorded by the launch once kappa_src has been read
     const int32_t* item_order;    // [J*T] (job, type) items: queue q holds [queue_off[q], queue_off[q+1])
-    unsigned long long* queue;    // [kQueues] next item of each queue (zeroed before each launch)
+    unsigned long long* queue;    // [kQueues] next item of each queue (the launch zeroes them and the tallies)
     int32_t queue_off[kQueues + 1];
     int32_t n_items;              // J * T
     int32_t n_parts;              // blocks that share an item's counts (part p takes every n_parts-th, from the
@@ -95,7 +98,7 @@ struct ProxyArgs {
     const float* x;
     const float* q;               // all-to-all bytes per sample
     const TypeDev* types;         // [T]
-    const double* hbm;            // [T] memory bandwidth, bytes/s
+    double hbm[kMaxTypes];        // memory bandwidth by type, bytes/s (by value: a call uploads nothing)
     const int32_t* counts;        // [NC]
     const float* kappa;           // [T*NC]
     // multisets of s powers of two summing to counts[c], exponents at bits
