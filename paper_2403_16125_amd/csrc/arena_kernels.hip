@@ -1045,6 +1045,15 @@ __device__ __forceinline__ bool ext_ok(const ExtCtx& E, const double* U, const d
     return U[e * S] - U[i * S] <= tS && P <= tP && mem <= E.mem;
 }
 
+// Does stage [i, e) fit memory with infl microbatches in flight?  (The test of
+// ext_ok, same operation order; it holds on a prefix of the ends e.)
+__device__ __forceinline__ bool ext_fits(const ExtCtx& E, const double* Pp, const double* Ap, int i, int e, int infl)
+{
+    const double P = Pp[e] - Pp[i];
+    const double Am = Ap[e] - Ap[i];
+    return 4.0 * P / E.tpd + (double)infl * E.b * Am / E.tpd <= E.mem;
+}
+
 // Suffix recursion over the splits within the thresholds, rows t = 1..tmax
 // into H (L + 1 doubles, in place: row t at i reads row t-1 only right of i):
 //   KIND 0: H_t(i) = least X of layers [i, L) as the last t stages,
@@ -1053,58 +1062,70 @@ __device__ __forceinline__ bool ext_ok(const ExtCtx& E, const double* U, const d
 //           H_1(i) = P(i, L), H_t(i) = min_e max(P(i, e), H_{t-1}(e));
 //   KIND 2: the same with the stages' per-sample costs;
 // over the ends e whose stage [i, e) is allowed as stage pp - t (+inf: none).
-// Returns H_tmax(0).  Lanes own i = lane and lane + 64 and scan their ends in
-// step, stopping at the first stage not allowed.
+// Returns H_tmax(0).  Lanes own i = lane and lane + 64.  The allowed ends are a
+// prefix: the last one is bisected once and only moves left as t grows (more
+// microbatches in flight), so a row's scan tests nothing but the recursion
+// (testing each end of each row had cost two divisions an end; 512 trace-like
+// jobs x 140 grids, with the thresholds skipped below: 26.0 -> 5.5 ms).  KIND 1 and 2
+// stop where the stage alone reaches the best (it only grows with e).
 template <int S, int KIND>
 __device__ double ext_rows(const ExtCtx& E, const double* U, const double* Pp, const double* Ap, const float* x,
                            double* H, int lane, double tS, double tP, int tmax)
 {
-    const int L = E.L, pp = E.pp;
+    const int L = E.L;
+    int reach[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int i = lane + 64 * h;
+        int lo = i;                     // the last end allowed for a last stage (i: none)
+        if (i < L) {
+            const double Ui = U[i * S], Pi = Pp[i];
+            int hi = L;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (U[mid * S] - Ui <= tS && Pp[mid] - Pi <= tP && ext_fits(E, Pp, Ap, i, mid, 1))
+                    lo = mid;
+                else
+                    hi = mid - 1;
+            }
+        }
+        reach[h] = lo;
         if (i <= L) {
             double v = kInf;
-            if (i < L && ext_ok<S>(E, U, Pp, Ap, i, L, pp - 1, tS, tP))
-                v = KIND == 0 ? 0.0 : (KIND == 1 ? Pp[L] - Pp[i] : U[L * S] - U[i * S]);
+            if (i < L && lo == L) v = KIND == 0 ? 0.0 : (KIND == 1 ? Pp[L] - Pp[i] : U[L * S] - U[i * S]);
             H[i] = v;
         }
     }
     wave_sync();
     for (int t = 2; t <= tmax; ++t) {
-        const int k = pp - t, last = L - t + 1;
-        const int i0 = lane, i1 = lane + 64;
-        double b0 = kInf, b1 = kInf;
-        bool g0 = i0 <= L - t, g1 = i1 <= L - t;
-        int e0 = i0 + 1, e1 = i1 + 1;
-        while (g0 || g1) {
-            if (g0) {
-                if (e0 > last || !ext_ok<S>(E, U, Pp, Ap, i0, e0, k, tS, tP)) {
-                    g0 = false;
+        double best[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int i = lane + 64 * h;
+            best[h] = kInf;
+            if (i <= L - t) {
+                if (t <= E.m)
+                    while (reach[h] > i && !ext_fits(E, Pp, Ap, i, reach[h], t)) --reach[h];
+                const int top = reach[h] < L - t + 1 ? reach[h] : L - t + 1;
+                double bv = kInf;
+                if (KIND == 0) {
+                    for (int e = i + 1; e <= top; ++e) bv = fmin(bv, (double)x[e - 1] + H[e]);
                 } else {
-                    const double h = H[e0];
-                    if (h < kInf)
-                        b0 = fmin(b0, KIND == 0 ? (double)x[e0 - 1] + h
-                                                : fmax(KIND == 1 ? Pp[e0] - Pp[i0] : U[e0 * S] - U[i0 * S], h));
-                    ++e0;
+                    const double base = KIND == 1 ? Pp[i] : U[i * S];
+                    for (int e = i + 1; e <= top; ++e) {
+                        const double v = (KIND == 1 ? Pp[e] : U[e * S]) - base;
+                        if (v >= bv) break;
+                        bv = fmin(bv, fmax(v, H[e]));
+                    }
                 }
-            }
-            if (g1) {
-                if (e1 > last || !ext_ok<S>(E, U, Pp, Ap, i1, e1, k, tS, tP)) {
-                    g1 = false;
-                } else {
-                    const double h = H[e1];
-                    if (h < kInf)
-                        b1 = fmin(b1, KIND == 0 ? (double)x[e1 - 1] + h
-                                                : fmax(KIND == 1 ? Pp[e1] - Pp[i1] : U[e1 * S] - U[i1 * S], h));
-                    ++e1;
-                }
+                best[h] = bv;
             }
         }
         // every lane has read row t-1 before any lane overwrites it
         __asm__ volatile("" ::: "memory");
-        if (i0 <= L) H[i0] = i0 <= L - t ? b0 : kInf;
-        if (i1 <= L) H[i1] = i1 <= L - t ? b1 : kInf;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (lane + 64 * h <= L) H[lane + 64 * h] = best[h];
         wave_sync();
     }
     const double r = H[0];
@@ -1134,51 +1155,103 @@ __device__ double ext_next(const double* V, int lane, int L, double th)
     return wave_reduce1<OpMin>(best);
 }
 
-// Exact-T key of one plan (false: no split fits).  Thresholds are visited by
-// tS then tP ascending; each pair's least X gives the key ((cS tS + cX X) +
-// cP tP, tS, tP, X), and the least key over the pairs is the least key over
-// the splits.  A pair after the best key found so far wins only with a
-// smaller Phi, so the visit stops where a lower bound of Phi reaches the best:
+// Exact-T key of one plan (false: no split fits with a Phi of at most `cap`).
+// Thresholds are visited by tS then tP ascending; each pair's least X gives the
+// key ((cS tS + cX X) + cP tP, tS, tP, X), and the least key over the pairs is
+// the least key over the splits.  A pair after the best key found so far wins
+// only with a smaller Phi, so the visit stops where a lower bound of Phi reaches
+// the best:
 //   tS runs from the least Smax of any split that fits and stops once (cS tS
 //   + cX Xlo) + cP Plo reaches the best (Xlo, Plo the least X and Pmax of any
 //   split that fits), or, when cS = 0, once the best is the least Phi of any
 //   split;
 //   tP runs from the least Pmax within tS and stops once (cS tS + cX Xs) +
 //   cP tP reaches the best (Xs the least X within tS) or its X is Xs.
+// A run of thresholds [t, e] is skipped whole when the least X (and Pmax) within
+// e with t itself does not beat the best: both fall as thresholds grow, and Phi
+// is evaluated by operations that keep order, so no pair of the run does.  Runs
+// grow fourfold while they are skipped and shrink when one is not.
 template <int S>
 __device__ bool ext_solve(const ExtCtx& E, const double* U, const double* Pp, const double* Ap, const float* x,
-                          double* H, int lane, ExtKey& best)
+                          double* H, int lane, double cap, ExtKey& best)
 {
-    const double p_lo = ext_rows<S, 1>(E, U, Pp, Ap, x, H, lane, kInf, kInf, E.pp);
-    if (!(p_lo < kInf)) return false;
     const double s_lo = ext_rows<S, 2>(E, U, Pp, Ap, x, H, lane, kInf, kInf, E.pp);
+    if (!(s_lo < kInf) || ext_phi(E, s_lo, 0.0, 0.0) > cap) return false;
+    const double p_lo = ext_rows<S, 1>(E, U, Pp, Ap, x, H, lane, kInf, kInf, E.pp);
     const double x_lo = ext_rows<S, 0>(E, U, Pp, Ap, x, H, lane, kInf, kInf, E.pp);
+    bool found = false;
+    auto beats = [&](double phi) { return found ? phi < best.phi : phi <= cap; };
+    if (!beats(ext_phi(E, s_lo, x_lo, p_lo))) return false;
+    auto least_x = [&](double tS, double tP) { return ext_rows<S, 0>(E, U, Pp, Ap, x, H, lane, tS, tP, E.pp); };
     double phi_all = kInf;
     if (E.cS == 0.0) {
-        for (double tP = p_lo; tP < kInf; tP = ext_next<1>(Pp, lane, E.L, tP)) {
-            const double X = ext_rows<S, 0>(E, U, Pp, Ap, x, H, lane, kInf, tP, E.pp);
-            if (X < kInf) phi_all = fmin(phi_all, (0.0 + E.cX * X) + E.cP * tP);
-            if (X == x_lo) break;
-        }
-    }
-    bool found = false;
-    for (double tS = s_lo; tS < kInf; tS = ext_next<S>(U, lane, E.L, tS)) {
-        if (found && (E.cS == 0.0 ? best.phi <= phi_all : ext_phi(E, tS, x_lo, p_lo) >= best.phi)) break;
-        const double pmin = ext_rows<S, 1>(E, U, Pp, Ap, x, H, lane, tS, kInf, E.pp);
-        if (!(pmin < kInf)) continue;
-        const double xs = ext_rows<S, 0>(E, U, Pp, Ap, x, H, lane, tS, kInf, E.pp);
-        for (double tP = pmin; tP < kInf; tP = ext_next<1>(Pp, lane, E.L, tP)) {
-            if (found && ext_phi(E, tS, xs, tP) >= best.phi) break;
-            const double X = ext_rows<S, 0>(E, U, Pp, Ap, x, H, lane, tS, tP, E.pp);
-            if (X < kInf) {
-                const ExtKey k = {ext_phi(E, tS, X, tP), tS, tP, X};
-                if (!found || ext_less(k, best)) {
-                    best = k;
-                    found = true;
+        // (0 + cX X) + cP tP over the parameter thresholds alone
+        double run = 0.0;
+        for (double tP = p_lo; tP < kInf;) {
+            if (run > 0.0) {
+                const double e = tP + run;
+                const double X = least_x(kInf, e);
+                if (ext_phi(E, 0.0, X, tP) >= phi_all) {
+                    if (X == x_lo) break;
+                    run *= 4.0;
+                    tP = ext_next<1>(Pp, lane, E.L, e);
+                    continue;
                 }
             }
-            if (X == xs) break;
+            const double X = least_x(kInf, tP);
+            if (X < kInf) phi_all = fmin(phi_all, ext_phi(E, 0.0, X, tP));
+            if (X == x_lo) break;
+            const double nx = ext_next<1>(Pp, lane, E.L, tP);
+            run = run > 0.0 ? run * 0.25 : 4.0 * (nx - tP);
+            tP = nx;
         }
+        if (phi_all > cap) return false;
+    }
+    double srun = 0.0;
+    for (double tS = s_lo; tS < kInf;) {
+        if (E.cS == 0.0 ? found && best.phi <= phi_all : !beats(ext_phi(E, tS, x_lo, p_lo))) break;
+        if (srun > 0.0) {
+            const double e = tS + srun;
+            const double pe = ext_rows<S, 1>(E, U, Pp, Ap, x, H, lane, e, kInf, E.pp);
+            if (!(pe < kInf) || !beats(ext_phi(E, tS, least_x(e, kInf), pe))) {
+                srun *= 4.0;
+                tS = ext_next<S>(U, lane, E.L, e);
+                continue;
+            }
+        }
+        const double pmin = ext_rows<S, 1>(E, U, Pp, Ap, x, H, lane, tS, kInf, E.pp);
+        if (pmin < kInf) {
+            const double xs = least_x(tS, kInf);
+            double prun = 0.0;
+            for (double tP = pmin; tP < kInf;) {
+                if (!beats(ext_phi(E, tS, xs, tP))) break;
+                if (prun > 0.0) {
+                    const double e = tP + prun;
+                    const double X = least_x(tS, e);
+                    if (!beats(ext_phi(E, tS, X, tP))) {
+                        if (X == xs) break;
+                        prun *= 4.0;
+                        tP = ext_next<1>(Pp, lane, E.L, e);
+                        continue;
+                    }
+                }
+                const double X = least_x(tS, tP);
+                if (X < kInf) {
+                    const ExtKey k = {ext_phi(E, tS, X, tP), tS, tP, X};
+                    if (found ? ext_less(k, best) : k.phi <= cap) {
+                        best = k;
+                        found = true;
+                    }
+                }
+                if (X == xs) break;
+                const double nx = ext_next<1>(Pp, lane, E.L, tP);
+                prun = prun > 0.0 ? prun * 0.25 : 4.0 * (nx - tP);
+                tP = nx;
+            }
+        }
+        const double nx = ext_next<S>(U, lane, E.L, tS);
+        srun = srun > 0.0 ? srun * 0.25 : 4.0 * (nx - tS);
+        tS = nx;
     }
     return found;
 }
@@ -1282,7 +1355,9 @@ __device__ double price_exact(const BlockLds& B, WaveLds& Wv, const double* U, i
             E.cX = cell.kappa * 2.0 * bm / cell.B_pp;
             E.cP = cP;
             ExtKey key;
-            if (ext_solve<S>(E, U, B.Pp, B.Ap, B.x, Wv.R, lane, key)) {
+            // a Phi past the window (a margin covers the rounding) is of no use
+            const double cap = lim < kInf ? (lim - bm * UL) + lim * 1e-13 : kInf;
+            if (ext_solve<S>(E, U, B.Pp, B.Ap, B.x, Wv.R, lane, cap, key)) {
                 // the stage costs sum to U_L; the cut-dependent rest is the key's Phi
                 T = bm * UL + key.phi;
                 best_t = fmin(best_t, T);
@@ -2096,8 +2171,8 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
                 E.cS = (double)(m - 1) * bw;
                 E.cX = cell.kappa * 2.0 * bw / cell.B_pp;
                 E.cP = dp > 1 ? cell.kappa * 2.0 * (double)(dp - 1) / (double)dp / ((double)tp * B_dp) : 0.0;
-                ExtKey key;
-                ext_solve<2>(E, U, B.Pp, B.Ap, B.x, Wv.R, lane, key);
+                ExtKey key = {};
+                ext_solve<2>(E, U, B.Pp, B.Ap, B.x, Wv.R, lane, (Tb - bw * U[2 * jb.L]) + Tb * 1e-13, key);
                 sg = ext_cuts<2>(E, U, B.Pp, B.Ap, B.x, Wv.R, lane, key);
             } else {
                 sg = canonical_stages<2>(U, Wv.J, lane, jb.L, pp, W);

@@ -153,3 +153,33 @@ def test_refused_beyond_its_layer_limit():
         assert ei.value.status == arena.ARENA_ERR_UNSUPPORTED
     finally:
         est.close()
+
+
+@pytest.mark.parametrize("kind", ["one_microbatch", "ties", "binding"])
+def test_runs_of_thresholds(oracle, kind):
+    """Jobs whose layers all differ in parameters and boundaries, so a plan has hundreds
+    of thresholds and runs of them are skipped: a single microbatch (the slowest stage
+    has no weight in the time, so the least-cost splits are told apart by it), equal
+    values (ties down to the cuts), memory that binds on some stages only."""
+    rng = np.random.default_rng(21)
+    L = 19
+    u = lambda lo, hi: list(np.round(rng.uniform(lo, hi, L)) if kind == "ties" else rng.uniform(lo, hi, L))
+    scale = 1e7 if kind == "ties" else 1.0
+    big = lambda v: [scale * e for e in v]
+    job = dict(t=[1e-3 * e for e in u(1, 4)], p=big(u(1, 4)) if kind == "ties" else u(5e7, 3e8),
+               a=big(u(1, 3)) if kind == "ties" else u(2e7, 9e7), x=big(u(1, 3)) if kind == "ties" else u(1e6, 4e7),
+               a2a=[0.0] * L, batch=64)
+    types = [dict(speed=1.0, mem=8e9 if kind == "binding" else 80e9, bw_intra=100e9, bw_inter=5e9, gpus_per_node=8),
+             dict(speed=0.5, mem=3e9 if kind == "binding" else 40e9, bw_intra=30e9, bw_inter=np.inf, gpus_per_node=4)]
+    w = wl.from_lists([job], types, [1, 2, 4, 8, 12, 16, 32], [1] if kind == "one_microbatch" else [1, 2, 8, 32],
+                      kappa=1.5)
+    est = arena.Estimator(w, with_cuts=True, rule=arena.PARTITION_EXACT_T)
+    try:
+        est.estimate()
+        res = est.results()
+    finally:
+        est.close()
+    rep = compare(w, res, np.arange(w.n_cells), oracle, rule=arena.PARTITION_EXACT_T)
+    _say(f"runs of thresholds, {kind}: exact={rep['exact']} near_tie={rep['near_tie']} infeasible={rep['infeasible']}")
+    assert not rep["mismatch"], rep["mismatch"][:5]
+    assert rep["near_tie"] == 0 and (kind != "binding" or 0 < rep["infeasible"] < rep["n"])
