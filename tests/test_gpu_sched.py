@@ -454,3 +454,46 @@ def test_fairness_bad_values_leave_everything_unchanged(bad):
         assert (r["launched"] == -7).all()
     finally:
         s.close()
+
+
+def _all_in_state(seed, n_run, n_queue, T, counts, depth, run_at, hole=None):
+    """n_run jobs running at count index `run_at` (dealt over the types), the rest queued;
+    `hole`: no throughput at the counts from 1 up to that index (a scale-down skips them)."""
+    J = n_run + n_queue
+    thr = ss.synthetic_thr(seed, J, T, counts)
+    if hole is not None:
+        thr[:n_run, :, 1:hole] = 0.0
+        thr[:n_run, :, 0] = 1.0
+    thr[:n_run, :, run_at] = np.maximum(thr[:n_run, :, run_at], 2.0)
+    at = np.where(np.arange(J) < n_run, np.arange(J) % T, -1).astype(np.int32)
+    ac = np.where(np.arange(J) < n_run, run_at, 0).astype(np.int32)
+    used = np.bincount(at[:n_run], minlength=T) * counts[run_at]
+    queue = np.arange(n_run, J, dtype=np.int32)
+    return ss.SchedState(thr=thr, counts=np.asarray(counts, np.int32), capacity=(used + 3).astype(np.int32),
+                         alloc_type=at, alloc_count=ac, queue=queue,
+                         priority=(np.arange(n_queue) * 3 // max(1, n_queue)).astype(np.int32), depth=depth)
+
+
+# name: (running, queued, types, counts, depth, running count index, hole)
+VISITS = {
+    "scaled_down_again_and_again": (3, 9, 2, list(range(1, 41)), 60, 30, None),   # past the steps known ahead
+    "closed_counts_below": (20, 20, 3, list(range(1, 31)), 5, 25, 20),            # past one round of loads
+    "slots_full": (1100, 52, 2, [1, 2, 4], 3, 1, None),                           # 1152 jobs: one wave decides
+    "slots_over": (1100, 53, 2, [1, 2, 4], 3, 1, None),                           # 1153: the block does
+    "row_fits": (40, 30, 20, list(range(1, 103)), 4, 9, None),                    # 2040 grids: a ring of 4
+    "row_over": (40, 30, 21, list(range(1, 99)), 4, 9, None),                     # 2058: the block visits
+    "one_grid": (2, 40, 1, [4], 2, 0, None),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["plain", "fair", "deadlines"])
+@pytest.mark.parametrize("name", sorted(VISITS))
+def test_visits_by_one_wave_and_by_the_block(name, kind):
+    n_run, n_queue, T, counts, depth, run_at, hole = VISITS[name]
+    st = _all_in_state(31, n_run, n_queue, T, counts, depth, run_at, hole)
+    ddl = None
+    if kind != "plain":
+        b, n, d = ss.deadlines(31, st.thr, slack=(0.9, 30.0))
+        ddl = (b, n, d if kind == "deadlines" else None)
+    _check(st, ddl, "throughput" if kind == "plain" else "fairness")
