@@ -1727,6 +1727,64 @@ __device__ __forceinline__ void stage_counts(const EstimateArgs& A, uint16_t* cn
     }
 }
 
+// Set-up: the largest admissible microbatch count of each data-parallel degree
+// (thread tid has degrees tid + 1 + 256 h, 0: none) and the ballots of the
+// admitted ones.  Below 2^20 samples the quotients come from float reciprocals
+// (relative error about 2^-23, so rounding gives the exact quotient of a divisor)
+// and a product check decides divisibility; larger batches take integer
+// remainders.
+__device__ __forceinline__ void admissible_counts(const EstimateArgs& A, int Bg, int tid, int wid, int lane,
+                                                  unsigned long long* group_ok, int (&mm)[kMaxDp / 256])
+{
+    const bool small_batch = Bg < (1 << 20);
+#pragma unroll
+    for (int h = 0; h < kMaxDp / 256; ++h) {
+        const int dp = h * 256 + tid + 1;
+        mm[h] = 0;
+        if (small_batch) {
+            const int q = (int)rintf((float)Bg * __builtin_amdgcn_rcpf((float)dp));
+            if (q * dp == Bg) {
+                for (int i = 0; i < A.n_m; ++i) {
+                    const int m = A.m_values[i];
+                    const int r = (int)rintf((float)q * __builtin_amdgcn_rcpf((float)m));
+                    if (r * m == q) mm[h] = m > mm[h] ? m : mm[h];
+                }
+            }
+        } else {
+            for (int i = 0; i < A.n_m; ++i)
+                if (Bg % (dp * A.m_values[i]) == 0) mm[h] = A.m_values[i] > mm[h] ? A.m_values[i] : mm[h];
+        }
+        const unsigned long long okm = __ballot(mm[h] != 0);
+        if (lane == 0) group_ok[h * kWavesPerBlock + wid] = okm;
+    }
+}
+
+// Set-up, after a barrier: the admitted data-parallel degrees, largest first,
+// each with its largest count from bit 16.
+__device__ __forceinline__ void list_degrees(const unsigned long long* group_ok, const int (&mm)[kMaxDp / 256], int tid,
+                                             int wid, uint32_t* dps, int32_t& n_dps)
+{
+    int total = 0, before[kMaxDp / 256] = {};
+#pragma unroll
+    for (int k = 0; k < kMaxDp / 64; ++k) {
+        const int c = __popcll(group_ok[k]);
+#pragma unroll
+        for (int h = 0; h < kMaxDp / 256; ++h)
+            if (k < h * kWavesPerBlock + wid) before[h] += c;
+        total += c;
+    }
+#pragma unroll
+    for (int h = 0; h < kMaxDp / 256; ++h)
+        if (mm[h] != 0) {
+            const unsigned long long okm = group_ok[h * kWavesPerBlock + wid];
+            const int rank = before[h] + __builtin_amdgcn_mbcnt_hi((unsigned)(okm >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((unsigned)okm, 0u));
+            if (total - 1 - rank < kMaxDps)
+                dps[total - 1 - rank] = (unsigned)(h * 256 + tid + 1) | ((unsigned)mm[h] << 16);
+        }
+    if (tid == 0) n_dps = total < kMaxDps ? total : kMaxDps;
+}
+
 // Counts of one part of an item: every n_parts-th, from the part-th largest.
 __device__ __forceinline__ int part_counts(const EstimateArgs& A, int part)
 {
@@ -1780,32 +1838,8 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         has_q = qv > 0.0f;
     }
     if (tid < kLmax + 4) B.wanted[tid] = 0;
-    // largest admissible microbatch count of each data-parallel degree.  Below
-    // 2^20 samples the quotients come from float reciprocals (relative error
-    // about 2^-23, so rounding gives the exact quotient of a divisor) and a
-    // product check decides divisibility; larger batches take integer remainders.
-    const bool small_batch = jb.Bg < (1 << 20);
     int mm[kMaxDp / 256];
-#pragma unroll
-    for (int h = 0; h < kMaxDp / 256; ++h) {
-        const int dp = h * 256 + tid + 1;
-        mm[h] = 0;
-        if (small_batch) {
-            const int q = (int)rintf((float)jb.Bg * __builtin_amdgcn_rcpf((float)dp));
-            if (q * dp == jb.Bg) {
-                for (int i = 0; i < A.n_m; ++i) {
-                    const int m = A.m_values[i];
-                    const int r = (int)rintf((float)q * __builtin_amdgcn_rcpf((float)m));
-                    if (r * m == q) mm[h] = m > mm[h] ? m : mm[h];
-                }
-            }
-        } else {
-            for (int i = 0; i < A.n_m; ++i)
-                if (jb.Bg % (dp * A.m_values[i]) == 0) mm[h] = A.m_values[i] > mm[h] ? A.m_values[i] : mm[h];
-        }
-        const unsigned long long okm = __ballot(mm[h] != 0);
-        if (lane == 0) B.group_ok[h * kWavesPerBlock + wid] = okm;
-    }
+    admissible_counts(A, jb.Bg, tid, wid, lane, B.group_ok, mm);
     jb.moe = __syncthreads_or(has_q) != 0;
     if (wid == 0 || wid == 1) {
         const float* src = (wid == 0 ? A.p : A.a) + off;
@@ -1844,28 +1878,7 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
             B.pure_cached[1] = 0ull;
         }
     }
-    // the admitted data-parallel degrees, largest first
-    {
-        int total = 0, before[kMaxDp / 256] = {};
-#pragma unroll
-        for (int k = 0; k < kMaxDp / 64; ++k) {
-            const int c = __popcll(B.group_ok[k]);
-#pragma unroll
-            for (int h = 0; h < kMaxDp / 256; ++h)
-                if (k < h * kWavesPerBlock + wid) before[h] += c;
-            total += c;
-        }
-#pragma unroll
-        for (int h = 0; h < kMaxDp / 256; ++h)
-            if (mm[h] != 0) {
-                const unsigned long long okm = B.group_ok[h * kWavesPerBlock + wid];
-                const int rank = before[h] + __builtin_amdgcn_mbcnt_hi((unsigned)(okm >> 32),
-                                                                      __builtin_amdgcn_mbcnt_lo((unsigned)okm, 0u));
-                if (total - 1 - rank < kMaxDps)
-                    B.dps[total - 1 - rank] = (unsigned)(h * 256 + tid + 1) | ((unsigned)mm[h] << 16);
-            }
-        if (tid == 0) B.n_dps = total < kMaxDps ? total : kMaxDps;
-    }
+    list_degrees(B.group_ok, mm, tid, wid, B.dps, B.n_dps);
     __syncthreads();
     const int n_dps = B.n_dps;
     const int n_pairs = B.n_tps * n_dps;
@@ -2293,8 +2306,9 @@ __device__ __forceinline__ double tab_lat(const double* vol, const double* lat, 
     return lat[k - 1] + (v - vol[k - 1]) * (lat[k] - lat[k - 1]) / (vol[k] - vol[k - 1]);
 }
 
-constexpr int kTabCacheBits = 8;
+constexpr int kTabCacheBits = 7;
 constexpr unsigned kTabCache = 1u << kTabCacheBits;   // bottleneck cache entries per block
+constexpr int kTabB = 32;   // microbatch sizes with tabulated communication sums: 2^(i/2), i even, 3 2^((i-3)/2), i odd
 
 struct TabBlockLds {
     float t[kLmax];
@@ -2310,6 +2324,15 @@ struct TabBlockLds {
     uint16_t cnt_i[kMaxCounts];
     int32_t next_cell;
     int32_t share;                    // one kappa for all counts of the type: bottlenecks are shared
+    uint32_t dps[kMaxDps];            // admitted data-parallel degrees, largest first (list_degrees)
+    unsigned long long group_ok[kMaxDp / 64];
+    uint8_t tps[kMaxTp];              // the node size's divisors
+    uint8_t mval[kMaxM];              // microbatch counts
+    int32_t n_tps, n_dps;
+    // least communication seconds of all layers per microbatch and unit of kappa,
+    // rounded down: tensor parallel by tensor degree, and (row 0, whose degree is 1)
+    // all-to-all
+    float c_comm[kMaxTp][kTabB];
     double Upure[kLmax + kPad];       // prefix of the pure-compute per-sample cost (+inf padded)
     double Wpure[kLmax + 1];          // its bottleneck by degree (every degree up to the layer count)
     double head_p[kHeadLayers];       // parameter and activation bytes of the leading layers, as prefix
@@ -2460,67 +2483,63 @@ __device__ __forceinline__ double tab_price(const TabBlockLds& B, WaveLds& Wv, i
     return rs[0] + (double)(m - 1) * rm[0] + rm[1];
 }
 
-// Lower bound of the time of plan (dp, tp, pp, m) over every split, or +inf
-// when no split can fit memory, from its per-microbatch costs alone: the
-// stages tile the layers (W_max >= sum c / pp and >= max c), each of the pp-1
-// boundaries moves at least the smallest boundary activation, the largest
-// stage holds at least max(P / pp, max p_l) of parameters, and f is
-// non-decreasing.  A relative margin of 1e-9 covers the sums' rounding.
-// The sum and the largest of the per-microbatch costs depend on the plan only
-// through (tp, b, dp tp > 1): the wave keeps those of the cell's current tp in
-// a small table in its UD row (unused until the plans are priced): keys at
-// [0, 64) (b, negated when dp tp = 1), sums at [64, 128), largest at [128, 192);
-// `nc` entries (uniform).
-__device__ __forceinline__ double tab_bound(const TabBlockLds& B, WaveLds& Wv, int lane, const JobCtx& jb,
-                                            const TypeDev& ty, int K, const Cell& cell, int dp, int tp, int pp,
-                                            int m, double b, int& nc)
+// Place of microbatch size b in the communication sums: the largest tabulated
+// size not above b (latencies do not fall with the volume, so its sums bound
+// b's; powers of two and three times them are exact).
+__device__ __forceinline__ int tab_b_index(double b)
 {
-    const double plb = fmax(B.Pp[jb.L] / (double)pp, B.p_layer_max);
-    if (4.0 * plb > ty.mem * (double)tp * (1.0 + 1e-9)) return kInf;
-    // the stage holding layer l (l <= kHeadLayers) has at most l - 1 stages
-    // before it: at least min(m, pp - l + 1) microbatches in flight, and that
-    // layer's own bytes lower-bound its memory term by term
+    const unsigned u = __float_as_uint((float)b);
+    const int i = ((int)(u >> 23) - 127) * 2 + (int)((u >> 22) & 1u);
+    return i < kTabB ? i : kTabB - 1;
+}
+
+// Lower bound of the time of plan `key` (pp << 12 | tp << 7 | m) over every
+// split, or +inf when no split can fit memory; one plan per lane.  The stages
+// tile the layers, so the slowest is at least the sum over pp; the stage of
+// largest pure-compute cost reaches Wpure(pp) per sample and tensor degree 1 and
+// holds a layer, whose all-reduces are at least those of the least x; each of
+// the pp-1 boundaries moves at least the smallest boundary activation; the
+// largest stage holds at least max(P / pp, max p_l) of parameters; the stage
+// holding layer l (l <= kHeadLayers) has at most l - 1 stages before it, so at
+// least min(m, pp - l + 1) microbatches of that layer's bytes in flight; f is
+// non-decreasing.  Relative margins of 1e-9 cover reciprocal estimates and the
+// sums' rounding.  1024 jobs x 8 types x 131 counts: 45.0 ms when the wave took one
+// plan after another and summed the layers' costs per (tp, b) of every cell, 18.9
+// ms with the sums tabulated per item and Wpure in the bound.
+__device__ __forceinline__ double tab_bound(const TabBlockLds& B, const JobCtx& jb, const TypeDev& ty, int K,
+                                            const Cell& cell, unsigned key)
+{
+    const int pp = (int)(key >> 12), tp = (int)((key >> 7) & 0x1Fu), m = (int)(key & 0x7Fu);
+    const int dp = exact_quot(cell.n, tp * pp);
+    const double b = rint((double)jb.Bg * rcp_approx((double)(dp * m)));   // exact: dp m divides Bg
+    const double rpp = rcp_approx((double)pp);
+    const double rtp = tp == 1 ? 1.0 : rcp_approx((double)tp);
+    const double plb = fmax(B.Pp[jb.L] * rpp, B.p_layer_max);
+    const double cap = ty.mem * (double)tp * (1.0 + 1e-9);
+    bool over = 4.0 * plb > cap;
 #pragma unroll
     for (int l = 1; l <= kHeadLayers; ++l) {
         const int r = pp - l + 1;
         const int f = m < r ? m : (r > 1 ? r : 1);
-        const double memb = 4.0 * B.head_p[l - 1] / (double)tp + (double)f * b * B.head_a[l - 1] / (double)tp;
-        if (!(memb <= ty.mem)) return kInf;
+        over |= 4.0 * B.head_p[l - 1] + (double)f * b * B.head_a[l - 1] > cap;
     }
-    const double key = dp * tp > 1 ? b : -b;
-    const unsigned long long hit = __ballot(lane < nc && Wv.UD[lane] == key);
-    double UL, cmax;
-    if (hit) {
-        const int e = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hit));
-        UL = Wv.UD[64 + e];
-        cmax = Wv.UD[128 + e];
-    } else {
-        double c[2];
-        tab_layer_costs(B, lane, jb, ty, K, cell.kappa, dp, tp, b, c);
-        double rs[1] = {c[0] + c[1]};
-        double rm[1] = {fmax(c[0], c[1])};
-        wave_reduce<OpSum, 1>(rs);
-        wave_reduce<OpMax, 1>(rm);
-        UL = rs[0];
-        cmax = rm[0];
-        tally(Wv, lane, kAlgOps, 4ull * (unsigned)jb.L);
-        if (nc < 64) {
-            if (lane == 0) {
-                Wv.UD[nc] = key;
-                Wv.UD[64 + nc] = UL;
-                Wv.UD[128 + nc] = cmax;
-            }
-            wave_sync();
-            ++nc;
-        }
+    if (over) return kInf;
+    const int ib = tab_b_index(b);
+    double UL = b * B.Upure[jb.L] * rtp;
+    double Wlb = b * B.Wpure[pp] * rtp;
+    if (tp > 1) {
+        UL += cell.kappa * (double)B.c_comm[__popc(ty.divs & ((1u << tp) - 1u))][ib];
+        Wlb += cell.kappa * 4.0 *
+               tab_lat(B.vol[0], B.lat[0], K, 2.0 * (double)(tp - 1) * rtp * b * B.x_layer_min * (1.0 - 1e-9));
     }
-    const double Wlb = fmax(UL / (double)pp, cmax);
+    if (dp * tp > 1) UL += cell.kappa * (double)B.c_comm[0][ib];
+    Wlb = fmax(Wlb, UL * rpp);
     const int lpp = cell.n <= ty.gpn ? 0 : 1;
-    const int grp = dp * tp;
-    const int ldp = tiles_node(ty, grp) ? 0 : 1;
+    const int ldp = tiles_node(ty, dp * tp) ? 0 : 1;
     const double p2p = pp > 1 ? cell.kappa * (2.0 * tab_lat(B.vol[lpp], B.lat[lpp], K, b * B.x_layer_min)) : 0.0;
     const double ar = dp > 1
-        ? cell.kappa * tab_lat(B.vol[ldp], B.lat[ldp], K, 2.0 * (double)(dp - 1) / (double)dp * (plb / (double)tp))
+        ? cell.kappa * tab_lat(B.vol[ldp], B.lat[ldp], K,
+                               2.0 * (double)(dp - 1) * rcp_approx((double)dp) * (plb * rtp) * (1.0 - 1e-9))
         : 0.0;
     return (UL + (double)(pp - 1) * p2p + (double)(m - 1) * Wlb + ar) * (1.0 - 1e-9);
 }
@@ -2575,6 +2594,9 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         B.x[tid] = A.x[off + tid];
         B.q[tid] = A.q[off + tid];
     }
+    int mm[kMaxDp / 256];
+    admissible_counts(A, jb.Bg, tid, wid, lane, B.group_ok, mm);
+    if (tid < A.n_m) B.mval[tid] = (uint8_t)A.m_values[tid];
     if (tid < 2 * K) {
         const int link = tid / K, k = tid - link * K;
         const long long base = ((long long)g * 2 + link) * K + k;
@@ -2615,6 +2637,11 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         for (int c = lane; c < A.n_counts; c += 64) same &= A.kappa[g * A.n_counts + c] == A.kappa[g * A.n_counts];
         const bool uni = __ballot(!same) == 0ull;
         for (int h = lane; h < (int)kTabCache; h += 64) B.ckey[h] = 0u;
+        // the type's tensor degrees
+        const bool td = lane < 32 && ((ty.divs >> lane) & 1u);
+        const unsigned tdm = (unsigned)__ballot(td);
+        if (td) B.tps[__popc(tdm & ((1u << lane) - 1u))] = (uint8_t)lane;
+        if (lane == 0) B.n_tps = __popc(tdm);
         if (lane == 0) {
             B.share = (uni && A.n_counts > 1 && jb.Bg < (1 << 17)) ? 1 : 0;
             B.pure_cached[0] = 0ull;
@@ -2624,7 +2651,33 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
     if (tid == 0) B.next_cell = 0;
     if (wid == 0) tally(Wv, lane, kCells, (unsigned long long)part_counts(A, part));
     __syncthreads();
+    list_degrees(B.group_ok, mm, tid, wid, B.dps, B.n_dps);
+    // communication sums by tensor degree (row 0: the all-to-all's) and
+    // microbatch size, the sizes up to the batch
+    {
+        const int top = tab_b_index((double)jb.Bg) + 1;
+        for (int z = wid; z < top * B.n_tps; z += kWavesPerBlock) {
+            const int r = z / top, ib = z - r * top;
+            const double b = ib & 1 ? 1.5 * (double)(1 << (ib >> 1)) : (double)(1 << (ib >> 1));
+            const int tp = B.tps[r];
+            const double f = r == 0 ? b : 2.0 * (double)(tp - 1) / (double)tp * b;
+            double v = 0.0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int l = lane + 64 * h;
+                if (l < jb.L)
+                    v += r == 0 ? tab_lat(B.vol[1], B.lat[1], K, f * (double)B.q[l])
+                                : 4.0 * tab_lat(B.vol[0], B.lat[0], K, f * (double)B.x[l]);
+            }
+            v = wave_reduce1<OpSum>(v);
+            if (lane == 0) B.c_comm[r][ib] = __double2float_rd(v * (1.0 - 1e-9));
+        }
+    }
+    __syncthreads();
     const bool share = B.share != 0;
+    const int n_dps = B.n_dps;
+    const int n_cand = B.n_tps * n_dps * A.n_m;        // (tensor degree, data-parallel degree, count) triples
+    const float r_nm = __builtin_amdgcn_rcpf((float)A.n_m), r_dps = __builtin_amdgcn_rcpf((float)n_dps);
 
     for (;;) {
         int lane;
@@ -2639,29 +2692,31 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         cell.kappa = (double)A.kappa[g * A.n_counts + ci];
         cell.B_pp = 0.0;
         cell.c_p2p = 0.0;
-        // the plans: keys and lower bounds
+        // the plans, a triple per lane, and their lower bounds, a plan per lane
         int np = 0, nskip = 0;
-        for (int tp = 1; tp <= cell.n && tp <= ty.gpn; ++tp) {
-            if (!tiles_node(ty, tp) || exact_quot(cell.n, tp) * tp != cell.n) continue;
-            const int qn = exact_quot(cell.n, tp);
-            int nc = 0;                     // the bounds' cost sums of this tp
-            for (int pp = 1; pp <= qn && pp <= jb.L; ++pp) {
-                const int dp = exact_quot(qn, pp);
-                if (dp * pp != qn) continue;
-                for (int mi = 0; mi < A.n_m; ++mi) {
-                    const int m = A.m_values[mi];
-                    const double dm = (double)(dp * m);
-                    const double bq = rint((double)jb.Bg * rcp_approx(dm));   // exact when dm divides Bg
-                    if (!(bq * dm == (double)jb.Bg)) continue;
-                    const double lb = A.prune ? tab_bound(B, Wv, lane, jb, ty, K, cell, dp, tp, pp, m, bq, nc) : 0.0;
-                    if (lane == 0 && np < kMaxPlans) {
-                        Wv.planT[np] = lb;
-                        Wv.planKey[np] = ((unsigned)pp << 12) | ((unsigned)tp << 7) | (unsigned)m;
-                    }
-                    ++np;
-                }
+        for (int e0 = 0; e0 < n_cand; e0 += 64) {
+            const int e = e0 + lane;
+            unsigned key = 0u;
+            if (e < n_cand) {
+                const int pe = (int)(((float)e + 0.5f) * r_nm);
+                const int m = B.mval[e - pe * A.n_m];
+                const int ti = (int)(((float)pe + 0.5f) * r_dps);
+                const int tp = B.tps[ti], dp = (int)(B.dps[pe - ti * n_dps] & 0xFFFFu);
+                const int pp = (int)rintf((float)cell.n * __builtin_amdgcn_rcpf((float)(tp * dp)));
+                const double dm = (double)(dp * m);
+                const double bq = rint((double)jb.Bg * rcp_approx(dm));   // exact when dm divides Bg
+                if (__umul24(pp, tp * dp) == (unsigned)cell.n && pp <= jb.L && bq * dm == (double)jb.Bg)
+                    key = ((unsigned)pp << 12) | ((unsigned)tp << 7) | (unsigned)m;
             }
+            const unsigned long long okm = __ballot(key != 0u);
+            const int at = np + __builtin_amdgcn_mbcnt_hi((unsigned)(okm >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((unsigned)okm, 0u));
+            if (key != 0u && at < kMaxPlans) Wv.planKey[at] = key;
+            np += __popcll(okm);
         }
+        wave_sync();
+        for (int e = lane; e < np && e < kMaxPlans; e += 64)
+            Wv.planT[e] = A.prune ? tab_bound(B, jb, ty, K, cell, Wv.planKey[e]) : 0.0;
         if (np > kMaxPlans) {
             tally(Wv, lane, kOverflow, 1);
             np = kMaxPlans;

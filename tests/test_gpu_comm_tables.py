@@ -181,3 +181,37 @@ def test_shared_bottlenecks_are_exact():
         assert np.array_equal(r1[k][keep], r2[k][keep]), k
     _say(f"  recursions {c1['problems']} shared, {c2['problems']} unshared")
     assert c1["problems"] < c2["problems"]
+
+
+@pytest.mark.parametrize("batch", [96, 720720, 1 << 20, 7])
+def test_bounds_at_any_microbatch_size(oracle, batch):
+    """Microbatch sizes off the tabulated ones (odd multiples, beyond the largest), batches
+    with many divisors (several lists of plans per cell), large batches whose divisors come
+    from integer remainders, tensor degrees that are no powers of two, a two-point table and
+    sixteen points: every cell against the oracle, and pruning on and off bitwise equal."""
+    rng = np.random.default_rng(17)
+    L = 37
+    job = dict(t=list(rng.lognormal(-5, 0.6, L)), p=list(rng.uniform(1e8, 4e8, L)), a=list(rng.uniform(2e4, 6e4, L)),
+               x=list(rng.uniform(1e3, 4e5, L)), a2a=[0.0 if i % 3 else 2e4 for i in range(L)], batch=batch)
+    types = [dict(speed=1.0, mem=12e9, bw_intra=300e9, bw_inter=25e9, gpus_per_node=30),
+             dict(speed=0.6, mem=40e9, bw_intra=64e9, bw_inter=12.5e9, gpus_per_node=24)]
+    w = wl.from_lists([job], types, [1, 6, 60, 360, 720, 1024], [1, 2], kappa=1.4)
+    vol = wl.COMM_VOLUMES if batch != 96 else tuple([0.0] + [2.0 ** (10 + 2 * k) for k in range(15)])
+    tables = wl.linear_tables(w) if batch == 7 else wl.comm_tables(w, volumes=vol)
+    out = []
+    for prune in (True, False):
+        est = arena.Estimator(w, with_cuts=True, prune=prune, comm_tables=tables)
+        try:
+            est.estimate()
+            out.append((est.results(), est.counters(), est.space_size()))
+        finally:
+            est.close()
+    (a, ca, size), (b, cb, _) = out
+    for k in ("t_iter", "thr", "plan", "cuts"):
+        assert np.array_equal(a[k], b[k]), k
+    assert cb["plans"] == size["plans"] and ca["plans"] + ca["plans_skipped"] == size["plans"]
+    rep = compare(w, a, np.arange(w.n_cells), oracle, tables=tables)
+    _say(f"batch {batch}: {size['max_plans_per_cell']} plans per cell, exact={rep['exact']} near_tie={rep['near_tie']} "
+         f"infeasible={rep['infeasible']}")
+    assert not rep["mismatch"], rep["mismatch"][:5]
+    assert rep["near_tie"] == 0
