@@ -219,10 +219,15 @@ hipError_t ensure_capacity(T** ptr, size_t* cap, size_t n)
     return e;
 }
 
-// A pinned staging buffer of at least n words that no copy still reads.
-hipError_t ensure_staging(int32_t** ptr, size_t* cap, hipEvent_t done, size_t n)
+// A pinned staging buffer of at least n words that no copy still reads.  Refused
+// while `stream` is captured: the copies would run at a replay only, and the
+// tables would pass for uploaded before that.
+hipError_t ensure_staging(int32_t** ptr, size_t* cap, hipEvent_t done, size_t n, hipStream_t stream)
 {
-    hipError_t e = hipEventSynchronize(done);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(stream, &capture);
+    if (e == hipSuccess && capture != hipStreamCaptureStatusNone) e = hipErrorStreamCaptureUnsupported;
+    if (e == hipSuccess) e = hipEventSynchronize(done);
     if (e != hipSuccess || (*cap >= n && *ptr)) return e;
     (void)hipHostFree(*ptr);
     *ptr = nullptr;
@@ -257,8 +262,9 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream, const float** kappa
         if ((e = ensure_capacity(&c->d_batch, &c->cap_batch, (size_t)c->n_jobs)))
             return fail(c, ARENA_ERR_OUT_OF_MEMORY, "job tables: %s", hipGetErrorString(e));
         const size_t no = (size_t)c->n_jobs + 1, nb = (size_t)c->n_jobs;
-        if ((e = ensure_staging(&c->h_jobs, &c->cap_hjobs, c->jobs_done, no + nb)))
-            return fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned job staging: %s", hipGetErrorString(e));
+        if ((e = ensure_staging(&c->h_jobs, &c->cap_hjobs, c->jobs_done, no + nb, stream)))
+            return e == hipErrorOutOfMemory ? fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned job staging")
+                                            : hip_fail(c, e, "job table staging");
         std::memcpy(c->h_jobs, c->off.data(), sizeof(int32_t) * no);
         std::memcpy(c->h_jobs + no, c->batch.data(), sizeof(int32_t) * nb);
         if ((e = hipMemcpyAsync(c->d_off, c->h_jobs, sizeof(int32_t) * no, hipMemcpyHostToDevice, stream)) ||
@@ -468,8 +474,9 @@ arena_status upload_orders(arena_ctx* c, hipStream_t stream)
     if ((e = ensure_capacity(&c->d_item_order, &c->cap_items, items)) ||
         (e = ensure_capacity(&c->d_count_order, &c->cap_corder, (size_t)c->n_counts)))
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "work order: %s", hipGetErrorString(e));
-    if ((e = ensure_staging(&c->h_order, &c->cap_horder, c->order_done, items + (size_t)c->n_counts)))
-        return fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned work order staging: %s", hipGetErrorString(e));
+    if ((e = ensure_staging(&c->h_order, &c->cap_horder, c->order_done, items + (size_t)c->n_counts, stream)))
+        return e == hipErrorOutOfMemory ? fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned work order staging")
+                                        : hip_fail(c, e, "work order staging");
     std::memcpy(c->h_order, c->h_iorder.data(), sizeof(int32_t) * items);
     std::memcpy(c->h_order + items, c->h_corder.data(), sizeof(int32_t) * c->n_counts);
     if ((e = hipMemcpyAsync(c->d_item_order, c->h_order, sizeof(int32_t) * items, hipMemcpyHostToDevice, stream)) ||

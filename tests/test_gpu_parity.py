@@ -397,3 +397,45 @@ def test_few_items_split_over_blocks(kind):
         for k in ("t_iter", "thr", "plan", "cuts"):
             assert np.array_equal(few[k].view(np.uint8), many[k][ids].view(np.uint8)), (kind, lim, k)
         assert cnt["cells"] == len(ids) and cnt["plans"] + cnt["plans_skipped"] == size["plans"]
+
+
+@pytest.mark.parametrize("pending", ["jobs", "order"])
+def test_capture_waits_for_tables(pending):
+    """An estimate whose job tables or work order still have to be uploaded is refused
+    while its stream is captured, and the next one outside a capture uploads them; an
+    estimate with its tables in place is captured and replayed among eager ones."""
+    import torch
+    w = wl.make("tiny")
+    est = arena.Estimator(w, with_cuts=True)
+    keys = ("t_iter", "thr", "plan", "cuts")
+    try:
+        est.estimate()
+        first = est.results()
+        if pending == "jobs":
+            arena.arena_bind_jobs(est.ctx, w.layer_offset, w.batch, est.t, est.p, est.a, est.x, est.a2a)
+        else:
+            arena.arena_set_plan_space(est.ctx, w.m_values, w.tie_eps)
+        _say(f"capture with the {pending} pending")
+        torch.cuda.synchronize()
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), capture_error_mode="relaxed"):
+            with pytest.raises(Exception, match="staging"):
+                est.estimate()
+        for out in (est.t_iter, est.thr, est.plan, est.cuts):
+            out.zero_()
+        est.estimate()
+        for k, v in est.results().items():
+            assert k not in keys or np.array_equal(v, first[k]), k
+        _say("capture with the tables in place")
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+            est.estimate()
+        for _ in range(3):
+            for out in (est.t_iter, est.thr, est.plan, est.cuts):
+                out.zero_()
+            graph.replay()
+            again = est.results()
+            for k in keys:
+                assert np.array_equal(again[k], first[k]), k
+            est.estimate()
+    finally:
+        est.close()
