@@ -219,14 +219,19 @@ hipError_t ensure_capacity(T** ptr, size_t* cap, size_t n)
     return e;
 }
 
-// A pinned staging buffer of at least n words that no copy still reads.  Refused
-// while `stream` is captured: the copies would run at a replay only, and the
-// tables would pass for uploaded before that.
-hipError_t ensure_staging(int32_t** ptr, size_t* cap, hipEvent_t done, size_t n, hipStream_t stream)
+// An error while `stream` is captured: a table's copy would run at a replay only,
+// and the table would pass for uploaded before that.
+hipError_t refuse_capture(hipStream_t stream)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    hipError_t e = hipStreamIsCapturing(stream, &capture);
-    if (e == hipSuccess && capture != hipStreamCaptureStatusNone) e = hipErrorStreamCaptureUnsupported;
+    const hipError_t e = hipStreamIsCapturing(stream, &capture);
+    return e == hipSuccess && capture != hipStreamCaptureStatusNone ? hipErrorStreamCaptureUnsupported : e;
+}
+
+// A pinned staging buffer of at least n words that no copy still reads.
+hipError_t ensure_staging(int32_t** ptr, size_t* cap, hipEvent_t done, size_t n, hipStream_t stream)
+{
+    hipError_t e = refuse_capture(stream);
     if (e == hipSuccess) e = hipEventSynchronize(done);
     if (e != hipSuccess || (*cap >= n && *ptr)) return e;
     (void)hipHostFree(*ptr);
@@ -321,6 +326,7 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream, const float** kappa
         // asynchronously on the caller's stream
         const size_t nk = (size_t)c->n_types * c->n_counts;
         const int s = c->kslot;
+        if (!kappa_up && (e = refuse_capture(stream))) return hip_fail(c, e, "kappa staging");
         if ((e = hipEventSynchronize(c->kappa_done[s]))) return hip_fail(c, e, "kappa slot wait");
         std::memcpy(c->h_kappa[s], c->kappa.data(), sizeof(float) * nk);
         if (kappa_up) {

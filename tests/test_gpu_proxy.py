@@ -175,3 +175,41 @@ def test_bounds_keep_every_choice(kind):
     _, want = _compare(w, np.arange(w.n_cells))
     fits = np.isfinite(want["T"])
     assert fits.any() and (kind != "tight" or not fits.all())
+
+
+def test_captured_and_refused_with_kappa_pending():
+    """A call whose tables are in place is captured, and replays give the eager results;
+    one whose contention factors still have to be uploaded is refused under capture and
+    takes them afterwards."""
+    import torch
+
+    from paper_2403_16125_amd import arena
+    w = wl.make("tiny")
+    est = arena.Estimator(w)
+    keys = ("p_t_iter", "p_thr", "p_plan")
+    outs = lambda: [getattr(est, k).cpu().numpy().copy() for k in keys]
+    try:
+        est.proxy_estimate()
+        first = outs()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+            est.proxy_estimate()
+        for _ in range(3):
+            for k in keys:
+                getattr(est, k).zero_()
+            graph.replay()
+            assert all(np.array_equal(a, b) for a, b in zip(outs(), first))
+            est.proxy_estimate()
+        est.set_kappa(np.asarray(w.kappa[0]) * np.float32(1.5))
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), capture_error_mode="relaxed"):
+            with pytest.raises(Exception, match="kappa staging"):
+                est.proxy_estimate()
+        est.proxy_estimate()
+        scaled = outs()
+        assert not np.array_equal(scaled[0], first[0])
+        est.set_kappa(w.kappa[0])
+        est.proxy_estimate()
+        assert all(np.array_equal(a, b) for a, b in zip(outs(), first))
+    finally:
+        est.close()
