@@ -267,7 +267,11 @@ arena_status arena_space_size_get(const arena_ctx* ctx, arena_space_size* out);
  *   plan    uint32  packed plan word (see ARENA_PLAN_*)
  *   cuts    uint8   nullable; row of cuts_stride bytes per cell holding the
  *                   first layer of stages 1..pp-1, then 0xFF.
- *                   cuts_stride >= max layers - 1 when cuts is not NULL. */
+ *                   cuts_stride >= max layers - 1 when cuts is not NULL.
+ * A captured call keeps the addresses of the context's tables and caches.  They
+ * stay where they are until jobs, grids or communication tables are bound or set
+ * anew or the context is destroyed, whatever rule, plan space, contention factors
+ * or workspace cap are set meanwhile. */
 arena_status arena_estimate(arena_ctx* ctx, float* t_iter, float* thr, uint32_t* plan,
                             uint8_t* cuts, int32_t cuts_stride, void* stream);
 
@@ -281,10 +285,10 @@ arena_status arena_estimate(arena_ctx* ctx, float* t_iter, float* thr, uint32_t*
  * + 4 T NC + 4 J T bytes plus the communication tables and about 2 KB, for J
  * jobs, T types and NC counts, plus 8448 bytes per estimate block: one block
  * per item up to four per compute unit, 8.3 MiB on 256 CUs; with fewer items
- * than that more blocks share an item when the cap leaves room for them).  The tables are
- * checked first, before the device is asked for its CU count.  INVALID_ARG
- * for a negative value.  arena_estimate also returns OUT_OF_MEMORY when a
- * device allocation fails. */
+ * than that more blocks share an item, as many as the cap left room for when the
+ * jobs and grids were first estimated).  The tables are checked first, before
+ * the device is asked for its CU count.  INVALID_ARG for a negative value.
+ * arena_estimate also returns OUT_OF_MEMORY when a device allocation fails. */
 arena_status arena_set_workspace_limit(arena_ctx* ctx, int64_t bytes);
 
 #define ARENA_NOALLOC_SCRATCH_BYTES (16u << 20)

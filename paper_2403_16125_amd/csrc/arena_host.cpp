@@ -89,6 +89,7 @@ struct arena_ctx {
     unsigned long long* d_queue = nullptr;      // the estimate and proxy kernels' item queue
     uint8_t* d_pcut = nullptr;                  // the estimate blocks' caches of pure-compute splits
     size_t cap_pcut = 0;
+    bool pcut_dirty = true;                     // jobs or grids bound since they were made
     int n_cus = 0;
     int32_t* h_jobs = nullptr;                  // pinned staging of the job tables and of the work order,
     int32_t* h_order = nullptr;                 //   reused once the copies from them are done
@@ -608,6 +609,7 @@ arena_status arena_bind_jobs(arena_ctx* c, const arena_jobs_desc* d)
     c->jobs_bound = true;
     c->jobs_checked = false;
     c->jobs_dirty = true;
+    c->pcut_dirty = true;
     c->order_dirty = true;
     c->horder_valid = false;
     c->size_valid = false;
@@ -666,6 +668,7 @@ arena_status arena_bind_grids(arena_ctx* c, const arena_grids_desc* d)
     c->grids_dirty = true;
     c->msets_dirty = true;
     c->kappa_dirty = true;
+    c->pcut_dirty = true;
     c->order_dirty = true;
     c->horder_valid = false;
     c->size_valid = false;
@@ -823,9 +826,24 @@ arena_status check_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
     return ARENA_OK;
 }
 
+// Blocks that the context makes split caches for: the most that any partition
+// rule or the tables take on the bound jobs and grids (estimate_parts: a part is
+// at least a count per wave), clipped to the workspace cap (with room left there
+// for the largest tables).  The rule, the tables, the plan space and the cap do
+// not enter once the caches are made, so none of them moves the buffer that a
+// captured estimate holds the address of.
+int cache_blocks(const arena_ctx* c)
+{
+    const int least = estimate_blocks(c, 1);
+    const int most = estimate_blocks(c, (c->n_counts + arena::kWavesPerBlock - 1) / arena::kWavesPerBlock);
+    if (c->ws_limit == 0) return most;
+    const int64_t tables = (int64_t)workspace_layout(c, 0).total + (int64_t)c->n_types * 4 * ARENA_MAX_COMM_POINTS * 8;
+    return (int)std::max<int64_t>(least, std::min<int64_t>(most, (c->ws_limit - tables) / arena::kPureCutBytes));
+}
+
 // Parts an item's counts are split into, each taken by a block of its own, when
-// the items alone leave resident block slots empty (1 otherwise, and when the
-// parts' split caches would not fit `limit` bytes of workspace; 0: no limit).
+// the items alone leave resident block slots empty (1 otherwise, and no more than
+// there are split caches for: `blocks` of them).
 // Every part repeats the item's set-up, so how far splitting pays depends on
 // what a cell costs beside it.  The exact-T rule, tables, and long jobs over many
 // counts have cells that recurse deep: parts down to one count per wave, four
@@ -838,15 +856,14 @@ arena_status check_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
 // 137 in 512, 219 in 1024; 64 jobs of up to 48 layers x 3 types x 7 counts: 67 us
 // in 192 blocks, 95 in 384; 32 jobs of 128 layers x 4 types x 8 counts: 61 us in
 // 128 blocks, 85 in 384.
-int estimate_parts(const arena_ctx* c, size_t limit)
+int estimate_parts(const arena_ctx* c, int64_t blocks)
 {
     const bool deep = c->partition_rule == ARENA_PARTITION_EXACT_T || (c->tab_k > 0 && c->n_counts > 8) ||
                       (c->max_layers > 96 && c->n_counts >= 64);
     const int64_t items = (int64_t)c->n_jobs * c->n_types, cus = std::max(c->n_cus, 1);
     const int64_t waves = arena::kWavesPerBlock;
     const int64_t most = deep ? (c->n_counts + waves - 1) / waves : c->n_counts / (2 * waves);
-    const int parts = (int)std::max<int64_t>(1, std::min(most, (deep ? 4 : 2) * cus / items));
-    return limit == 0 || workspace_layout(c, estimate_blocks(c, parts)).total <= limit ? parts : 1;
+    return (int)std::max<int64_t>(1, std::min({most, (deep ? 4 : 2) * cus / items, blocks / items}));
 }
 
 // Kernel arguments from the context, with the library-owned tables at the
@@ -925,16 +942,19 @@ arena_status arena_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
     if (c->n_cus == 0 &&
         (e = hipDeviceGetAttribute(&c->n_cus, hipDeviceAttributeMultiprocessorCount, c->device)))
         return hip_fail(c, e, "hipDeviceGetAttribute");
-    const int parts = estimate_parts(c, (size_t)c->ws_limit);
-    const Workspace ws = workspace_layout(c, estimate_blocks(c, parts));
+    const Workspace ws = workspace_layout(c, estimate_blocks(c, 1));
     if (c->ws_limit > 0 && ws.total > (size_t)c->ws_limit)
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "estimate: needs %zu bytes of device workspace (limit %lld)",
                     ws.total, (long long)c->ws_limit);
     const float* kappa_up = nullptr;
     st = ensure_device(c, stream, &kappa_up);
     if (st != ARENA_OK) return st;
-    if ((e = ensure_capacity(&c->d_pcut, &c->cap_pcut, (size_t)arena::kPureCutBytes * estimate_blocks(c, parts))))
-        return fail(c, ARENA_ERR_OUT_OF_MEMORY, "split caches: %s", hipGetErrorString(e));
+    if (c->pcut_dirty) {
+        if ((e = ensure_capacity(&c->d_pcut, &c->cap_pcut, (size_t)arena::kPureCutBytes * cache_blocks(c))))
+            return fail(c, ARENA_ERR_OUT_OF_MEMORY, "split caches: %s", hipGetErrorString(e));
+        c->pcut_dirty = false;
+    }
+    const int parts = estimate_parts(c, (int64_t)(c->cap_pcut / arena::kPureCutBytes));
     if (c->order_dirty && (st = upload_orders(c, stream)) != ARENA_OK) return st;
     if (c->tab_k > 0) {
         if (c->tab_dirty) {
@@ -984,7 +1004,8 @@ arena_status arena_estimate_noalloc(arena_ctx* c, float* t_iter, float* thr, uin
     if (c->n_cus == 0 &&
         (e = hipDeviceGetAttribute(&c->n_cus, hipDeviceAttributeMultiprocessorCount, c->device)))
         return hip_fail(c, e, "hipDeviceGetAttribute");
-    const int parts = estimate_parts(c, arena::kNoallocScratchBytes);
+    const int parts = estimate_parts(
+        c, (int64_t)((arena::kNoallocScratchBytes - ws0.total) / arena::kPureCutBytes));
     const Workspace ws = workspace_layout(c, estimate_blocks(c, parts));
     if (ws.total > arena::kNoallocScratchBytes)
         return fail(c, ARENA_ERR_OUT_OF_MEMORY,
