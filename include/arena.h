@@ -268,6 +268,9 @@ arena_status arena_space_size_get(const arena_ctx* ctx, arena_space_size* out);
  *   cuts    uint8   nullable; row of cuts_stride bytes per cell holding the
  *                   first layer of stages 1..pp-1, then 0xFF.
  *                   cuts_stride >= max layers - 1 when cuts is not NULL.
+ * While `stream` is captured, a call whose job tables, work order or contention
+ * factors are still to be uploaded is refused (the upload would run at a replay
+ * only): run one outside the capture first.
  * A captured call keeps the addresses of the context's tables and caches.  They
  * stay where they are until jobs, grids or communication tables are bound or set
  * anew or the context is destroyed, whatever rule, plan space, contention factors

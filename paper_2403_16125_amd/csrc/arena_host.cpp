@@ -327,7 +327,7 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream, const float** kappa
         // asynchronously on the caller's stream
         const size_t nk = (size_t)c->n_types * c->n_counts;
         const int s = c->kslot;
-        if (!kappa_up && (e = refuse_capture(stream))) return hip_fail(c, e, "kappa staging");
+        if ((e = refuse_capture(stream))) return hip_fail(c, e, "kappa staging");
         if ((e = hipEventSynchronize(c->kappa_done[s]))) return hip_fail(c, e, "kappa slot wait");
         std::memcpy(c->h_kappa[s], c->kappa.data(), sizeof(float) * nk);
         if (kappa_up) {

@@ -399,11 +399,14 @@ def test_few_items_split_over_blocks(kind):
         assert cnt["cells"] == len(ids) and cnt["plans"] + cnt["plans_skipped"] == size["plans"]
 
 
-@pytest.mark.parametrize("pending", ["jobs", "order"])
+@pytest.mark.parametrize("pending", ["jobs", "order", "kappa"])
 def test_capture_waits_for_tables(pending):
-    """An estimate whose job tables or work order still have to be uploaded is refused
-    while its stream is captured, and the next one outside a capture uploads them; an
-    estimate with its tables in place is captured and replayed among eager ones."""
+    """An estimate whose job tables, work order or contention factors still have to be
+    uploaded is refused while its stream is captured, and the next one outside a capture
+    uploads them; an estimate with its tables in place is captured and replayed among
+    eager ones."""
+    import dataclasses
+
     import torch
     w = wl.make("tiny")
     est = arena.Estimator(w, with_cuts=True)
@@ -413,8 +416,12 @@ def test_capture_waits_for_tables(pending):
         first = est.results()
         if pending == "jobs":
             arena.arena_bind_jobs(est.ctx, w.layer_offset, w.batch, est.t, est.p, est.a, est.x, est.a2a)
-        else:
+        elif pending == "order":
             arena.arena_set_plan_space(est.ctx, w.m_values, w.tie_eps)
+        else:
+            kappa = np.asarray(w.kappa[0]) * np.float32(1.5)
+            first, _, _ = _run(dataclasses.replace(w, kappa=kappa[None]))
+            est.set_kappa(kappa)
         _say(f"capture with the {pending} pending")
         torch.cuda.synchronize()
         with torch.cuda.graph(torch.cuda.CUDAGraph(), capture_error_mode="relaxed"):

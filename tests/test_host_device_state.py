@@ -131,3 +131,23 @@ def test_caches_stay_within_the_cap(stub, ctx):
     pinned = 4 * (3 + 2) + 4 * (16 + 131) + 8 * 8 + 2 * 4 * 8 * 131      # host staging is not counted by the cap
     assert stub.stub_live_bytes() - before - pinned <= limit
     assert stub.stub_blocks() >= 16 and stub.stub_faults() == 0
+
+
+@pytest.mark.parametrize("call", ["estimate", "proxy"])
+def test_pending_factors_are_refused_under_capture(stub, ctx, call):
+    """Contention factors that wait for their upload are not recorded into a graph (their
+    staging buffer is reused, and nothing would have been copied when the capture ends):
+    the call is refused, records nothing, and the next one outside takes the factors."""
+    run = dict(estimate=_estimate,
+               proxy=lambda c: arena.arena_proxy_estimate(c, np.full(8, 2e12), 1e14, 16, OUT, OUT, OUT))[call]
+    _bind(ctx)
+    run(ctx)
+    arena.arena_set_kappa(ctx, np.full(8 * 131, 1.5, np.float32))
+    launches, copies = stub.stub_launches(), stub.stub_recorded_copies()
+    stub.stub_capture(1)
+    with pytest.raises(arena.ArenaError, match="kappa staging"):
+        run(ctx)
+    stub.stub_capture(0)
+    assert stub.stub_launches() == launches and stub.stub_recorded_copies() == copies
+    run(ctx)
+    assert stub.stub_kappa(0) == 1.5 and stub.stub_kappa(8 * 131 - 1) == 1.5
