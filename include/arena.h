@@ -268,9 +268,9 @@ arena_status arena_space_size_get(const arena_ctx* ctx, arena_space_size* out);
  *   cuts    uint8   nullable; row of cuts_stride bytes per cell holding the
  *                   first layer of stages 1..pp-1, then 0xFF.
  *                   cuts_stride >= max layers - 1 when cuts is not NULL.
- * While `stream` is captured, a call whose job tables, work order or contention
- * factors are still to be uploaded is refused (the upload would run at a replay
- * only): run one outside the capture first.
+ * While `stream` is captured, a call with tables, work order or contention
+ * factors still to upload is refused and changes nothing (the upload would run at
+ * a replay only): run one outside the capture first.
  * A captured call keeps the addresses of the context's tables and caches.  They
  * stay where they are until jobs, grids or communication tables are bound or set
  * anew or the context is destroyed, whatever rule, plan space, contention factors
@@ -363,8 +363,8 @@ arena_status arena_get_counters(arena_ctx* ctx, arena_counters* out);
  *                    4 bits per stage (stage j at bits 4j); word 2: log2 of
  *                    each stage's tensor degree, same layout.  All zero when
  *                    infeasible.
- * Asynchronous on `stream`.  A job whose operators all have zero load has no
- * proxy plan.  Host checks (jobs, grids and plan space bound; hbm_bw, f_ref
+ * Asynchronous on `stream`; a captured stream as for arena_estimate.  A job whose
+ * operators all have zero load has no proxy plan.  Host checks (jobs, grids and plan space bound; hbm_bw, f_ref
  * and n_ops in range; output pointers; at most 2^31 - 1 cells; at most 1280
  * power-of-two splits of one count into one stage count) return an error
  * before anything is enqueued. */

@@ -220,20 +220,32 @@ hipError_t ensure_capacity(T** ptr, size_t* cap, size_t n)
     return e;
 }
 
-// An error while `stream` is captured: a table's copy would run at a replay only,
-// and the table would pass for uploaded before that.
-hipError_t refuse_capture(hipStream_t stream)
+// The first of the bindings' tables that a call would still have to upload, or
+// null.
+const char* pending_table(const arena_ctx* c)
 {
+    if (!c->dev_ready || c->jobs_dirty || !c->jobs_checked) return "job table staging";
+    if (c->grids_dirty) return "grid table staging";
+    return c->kappa_dirty ? "kappa staging" : nullptr;
+}
+
+// Refuses a call with a table still to upload (`what`, null: none) while
+// `stream` is captured: the copy would run at a replay only, and the table would
+// pass for uploaded before that.  Asked before the call releases or makes any
+// buffer, so that work recorded earlier in the capture keeps its own.
+arena_status refuse_capture(arena_ctx* c, const char* what, hipStream_t stream)
+{
+    if (!what) return ARENA_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(stream, &capture);
-    return e == hipSuccess && capture != hipStreamCaptureStatusNone ? hipErrorStreamCaptureUnsupported : e;
+    hipError_t e = hipStreamIsCapturing(stream, &capture);
+    if (e == hipSuccess && capture != hipStreamCaptureStatusNone) e = hipErrorStreamCaptureUnsupported;
+    return e == hipSuccess ? ARENA_OK : hip_fail(c, e, what);
 }
 
 // A pinned staging buffer of at least n words that no copy still reads.
-hipError_t ensure_staging(int32_t** ptr, size_t* cap, hipEvent_t done, size_t n, hipStream_t stream)
+hipError_t ensure_staging(int32_t** ptr, size_t* cap, hipEvent_t done, size_t n)
 {
-    hipError_t e = refuse_capture(stream);
-    if (e == hipSuccess) e = hipEventSynchronize(done);
+    hipError_t e = hipEventSynchronize(done);
     if (e != hipSuccess || (*cap >= n && *ptr)) return e;
     (void)hipHostFree(*ptr);
     *ptr = nullptr;
@@ -268,7 +280,7 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream, const float** kappa
         if ((e = ensure_capacity(&c->d_batch, &c->cap_batch, (size_t)c->n_jobs)))
             return fail(c, ARENA_ERR_OUT_OF_MEMORY, "job tables: %s", hipGetErrorString(e));
         const size_t no = (size_t)c->n_jobs + 1, nb = (size_t)c->n_jobs;
-        if ((e = ensure_staging(&c->h_jobs, &c->cap_hjobs, c->jobs_done, no + nb, stream)))
+        if ((e = ensure_staging(&c->h_jobs, &c->cap_hjobs, c->jobs_done, no + nb)))
             return e == hipErrorOutOfMemory ? fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned job staging")
                                             : hip_fail(c, e, "job table staging");
         std::memcpy(c->h_jobs, c->off.data(), sizeof(int32_t) * no);
@@ -327,7 +339,6 @@ arena_status ensure_device(arena_ctx* c, hipStream_t stream, const float** kappa
         // asynchronously on the caller's stream
         const size_t nk = (size_t)c->n_types * c->n_counts;
         const int s = c->kslot;
-        if ((e = refuse_capture(stream))) return hip_fail(c, e, "kappa staging");
         if ((e = hipEventSynchronize(c->kappa_done[s]))) return hip_fail(c, e, "kappa slot wait");
         std::memcpy(c->h_kappa[s], c->kappa.data(), sizeof(float) * nk);
         if (kappa_up) {
@@ -481,7 +492,7 @@ arena_status upload_orders(arena_ctx* c, hipStream_t stream)
     if ((e = ensure_capacity(&c->d_item_order, &c->cap_items, items)) ||
         (e = ensure_capacity(&c->d_count_order, &c->cap_corder, (size_t)c->n_counts)))
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "work order: %s", hipGetErrorString(e));
-    if ((e = ensure_staging(&c->h_order, &c->cap_horder, c->order_done, items + (size_t)c->n_counts, stream)))
+    if ((e = ensure_staging(&c->h_order, &c->cap_horder, c->order_done, items + (size_t)c->n_counts)))
         return e == hipErrorOutOfMemory ? fail(c, ARENA_ERR_OUT_OF_MEMORY, "pinned work order staging")
                                         : hip_fail(c, e, "work order staging");
     std::memcpy(c->h_order, c->h_iorder.data(), sizeof(int32_t) * items);
@@ -946,6 +957,10 @@ arena_status arena_estimate(arena_ctx* c, float* t_iter, float* thr, uint32_t* p
     if (c->ws_limit > 0 && ws.total > (size_t)c->ws_limit)
         return fail(c, ARENA_ERR_OUT_OF_MEMORY, "estimate: needs %zu bytes of device workspace (limit %lld)",
                     ws.total, (long long)c->ws_limit);
+    const char* pending = pending_table(c);
+    if (!pending && (c->order_dirty || c->pcut_dirty)) pending = "work order staging";
+    if (!pending && c->tab_k > 0 && c->tab_dirty) pending = "comm table staging";
+    if ((st = refuse_capture(c, pending, stream)) != ARENA_OK) return st;
     const float* kappa_up = nullptr;
     st = ensure_device(c, stream, &kappa_up);
     if (st != ARENA_OK) return st;
@@ -1168,6 +1183,9 @@ arena_status arena_proxy_estimate(arena_ctx* c, const arena_proxy_desc* d, float
     hipStream_t stream = (hipStream_t)stream_ptr;
     DeviceGuard guard(c->device);
     if (guard.status != hipSuccess) return hip_fail(c, guard.status, "hipSetDevice");
+    const char* pending = pending_table(c);
+    if (!pending && c->msets_dirty) pending = "proxy table staging";
+    if ((st = refuse_capture(c, pending, stream)) != ARENA_OK) return st;
     if ((st = ensure_device(c, stream)) != ARENA_OK) return st;
     hipError_t e;
     if (c->msets_dirty) {

@@ -133,13 +133,47 @@ def test_caches_stay_within_the_cap(stub, ctx):
     assert stub.stub_blocks() >= 16 and stub.stub_faults() == 0
 
 
+def _proxy(ctx):
+    arena.arena_proxy_estimate(ctx, np.full(8, 2e12), 1e14, 16, OUT, OUT, OUT)
+
+
+PENDING = {
+    "jobs": lambda c: _bind_jobs(c, 50, 40),
+    "grids": lambda c: _bind(c, n_counts=200),
+    "order": lambda c: arena.arena_set_plan_space(c, [1, 2, 4, 8], 1e-6),
+    "tables": lambda c: arena.arena_set_comm_tables(c, *_tables(8)),
+    "kappa": lambda c: arena.arena_set_kappa(c, np.full(8 * 131, 1.5, np.float32)),
+}
+
+
+@pytest.mark.parametrize("pending,call", [(p, _estimate) for p in sorted(PENDING)]
+                         + [(p, _proxy) for p in ("grids", "jobs", "kappa")])
+def test_a_refused_call_releases_nothing(stub, ctx, pending, call):
+    """A call that a capture refuses, for whatever is still to be uploaded, has neither
+    freed nor made a buffer before it (work recorded earlier in the capture holds
+    them) and records nothing."""
+    _bind(ctx)
+    _estimate(ctx)
+    _proxy(ctx)
+    PENDING[pending](ctx)
+    seen = lambda: (stub.stub_allocs(), stub.stub_frees(), stub.stub_launches(), stub.stub_recorded_copies())
+    before = seen()
+    stub.stub_capture(1)
+    with pytest.raises(arena.ArenaError, match="staging"):
+        call(ctx)
+    stub.stub_capture(0)
+    assert seen() == before
+    assert stub.stub_last_dangles() == 0
+    call(ctx)
+    assert stub.stub_faults() == 0
+
+
 @pytest.mark.parametrize("call", ["estimate", "proxy"])
 def test_pending_factors_are_refused_under_capture(stub, ctx, call):
     """Contention factors that wait for their upload are not recorded into a graph (their
     staging buffer is reused, and nothing would have been copied when the capture ends):
     the call is refused, records nothing, and the next one outside takes the factors."""
-    run = dict(estimate=_estimate,
-               proxy=lambda c: arena.arena_proxy_estimate(c, np.full(8, 2e12), 1e14, 16, OUT, OUT, OUT))[call]
+    run = dict(estimate=_estimate, proxy=_proxy)[call]
     _bind(ctx)
     run(ctx)
     arena.arena_set_kappa(ctx, np.full(8 * 131, 1.5, np.float32))
