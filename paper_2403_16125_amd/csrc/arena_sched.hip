@@ -111,7 +111,7 @@ struct SchedLds {
     unsigned long long rmask[2][kSchedWaves];
     unsigned long long rk64[2][kSchedWaves];
     int32_t log_job[kMaxSchedDepth];
-    int32_t log_cnt[kMaxSchedDepth];
+    int32_t log_cnt[kMaxSchedDepth];  // its count index before the move (decide: with its type from bit 16)
     int32_t log_slot[kMaxSchedDepth];
     double log_cost[kMaxSchedDepth];
     int32_t log_info[kMaxSchedDepth];
@@ -948,19 +948,22 @@ __device__ __forceinline__ void decide(const SchedArgs& A, SchedLds& S, int lam,
             kept += nlog;
         } else if (nlog) {
             // S4: undo, newest first (cached entries restored with them); a round of
-            // reads, then the stores of one move after the other
+            // reads, then the stores of one move after the other (a job moved more than
+            // once ends at its oldest entry: the fence keeps the moves' stores apart)
             for (int e0 = (nlog - 1) & ~63; e0 >= 0; e0 -= 64) {
                 const int e = e0 + lane < nlog ? e0 + lane : nlog - 1;
                 const int k = S.log_slot[e], al = S.log_cnt[e], i = S.log_job[e], info = S.log_info[e];
                 const double cost = S.log_cost[e];
                 const int top = nlog - e0 < 64 ? nlog - e0 : 64;
-                for (int u = top - 1; u >= 0; --u)
+                for (int u = top - 1; u >= 0; --u) {
                     if (lane == u) {
                         A.alloc_count[i] = al & 0xffff;
                         S.ralloc[k] = al;
                         F.cost[k] = cost;
                         F.info[k] = info;
                     }
+                    wave_fence();
+                }
             }
             fr = fr0;
             fit = fit0;

@@ -497,3 +497,38 @@ def test_visits_by_one_wave_and_by_the_block(name, kind):
         b, n, d = ss.deadlines(31, st.thr, slack=(0.9, 30.0))
         ddl = (b, n, d if kind == "deadlines" else None)
     _check(st, ddl, "throughput" if kind == "plain" else "fairness")
+
+
+def _long_undo_state():
+    """Three jobs at 31 GPUs of one type; the first queued job wants all 128 GPUs of a
+    96-GPU cluster, so every scale-down there is (90, several rounds of 64 log entries)
+    is made, each job moved 30 times, and undone; the next one fits the 3 free GPUs."""
+    counts = list(range(1, 41)) + [128]
+    thr = ss.synthetic_thr(37, 6, 1, counts)
+    thr[:3, 0] = np.sqrt(np.asarray(counts, np.float32)) * np.asarray([[3.0], [5.0], [7.0]], np.float32)
+    thr[3, 0, :40], thr[3, 0, 40] = 0.0, 50.0
+    thr[4, 0, 2:] = 0.0
+    return ss.SchedState(thr=thr, counts=np.asarray(counts, np.int32), capacity=np.asarray([96], np.int32),
+                         alloc_type=np.asarray([0, 0, 0, -1, -1, -1], np.int32),
+                         alloc_count=np.asarray([30, 30, 30, 0, 0, 0], np.int32),
+                         queue=np.asarray([3, 4, 5], np.int32), priority=np.asarray([0, 0, 0], np.int32), depth=200)
+
+
+def test_long_undo_state_makes_and_undoes_moves():
+    st = _long_undo_state()
+    want = so.schedule(st.thr, st.counts, st.capacity, st.alloc_type, st.alloc_count, st.queue, st.priority,
+                       st.depth)
+    assert want["launched"][0] == 0 and want["decisions"] > 180
+    # the queued jobs behind it see the running jobs where they were
+    assert all(c >= 30 - want["moves"][0] for c in want["alloc_count"][:3])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["plain", "fair"])
+def test_undo_of_jobs_moved_many_times(kind):
+    st = _long_undo_state()
+    if kind == "plain":
+        _check(st)
+    else:
+        b, n, _ = ss.deadlines(37, st.thr, slack=(0.9, 30.0))
+        _check(st, (b, n, None), "fairness")
