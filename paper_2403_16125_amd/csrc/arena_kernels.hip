@@ -1998,8 +1998,13 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
                 const float lim = __double2float_ru(best * (1.0 + A.tie_eps));
                 return A.prune ? of & __ballot(lb < __builtin_huge_valf() && lb <= lim) : of;
             };
-            // the target of least bound among `of` (not empty)
+            // the target of least bound among `of` (not empty).  Without pruning every
+            // target is priced: a problem's deepest degrees first (the list's last), so
+            // that the first certificate that fails leaves the rest to the recursion (in
+            // bound order 512 mixture-of-experts jobs x 4 types x 10 counts took 1069 us,
+            // deepest first they take 953)
             auto least = [&](unsigned long long of) -> int {
+                if (!A.prune) return 63 - __builtin_clzll(of);
                 const bool in = ((of >> lane) & 1ull) != 0ull;
                 const float lb = Wv.tlb[lane];
                 const float v = wave_min_f32(in ? lb : __builtin_huge_valf());
