@@ -45,8 +45,9 @@ constexpr int kLevels = 7;         // successor tables: 2^7 > largest stage coun
 constexpr int kLevelStride = 132;  // bytes per successor table (>= kLmax + 1)
 constexpr int kMaxTp = 8;          // tensor degrees of one type (divisors of a node size <= 31)
 constexpr int kMaxDps = 240;       // data-parallel degrees of one job: divisors <= 1024 of a batch below
-                                   // 2^31 (233 at most, for 1,396,755,360)
+                                   // 2^31 (233 at most, for 1,396,755,360), no larger than the largest count
 constexpr int kTargets = 64;       // plans' (pp, tp, dp) a wave bounds and orders at a time
+constexpr int kWantedTests = 1 << 16;  // (pair, count) tests at set-up up to which the requested degrees are looked for
 static_assert(kMaxPlans <= 256, "plan entries are packed below the key in 8 bits");
 constexpr int kCertMinDegree = 2;  // a bottleneck certificate is tried for degrees from here up
 constexpr int kHeadLayers = 2;     // leading layers whose own memory bounds every plan (lower bounds)
@@ -1729,11 +1730,12 @@ __device__ __forceinline__ void stage_counts(const EstimateArgs& A, uint16_t* cn
 
 // Set-up: the largest admissible microbatch count of each data-parallel degree
 // (thread tid has degrees tid + 1 + 256 h, 0: none) and the ballots of the
-// admitted ones.  Below 2^20 samples the quotients come from float reciprocals
+// admitted ones, of those up to the largest count `top` (no larger degree has a
+// plan).  Below 2^20 samples the quotients come from float reciprocals
 // (relative error about 2^-23, so rounding gives the exact quotient of a divisor)
 // and a product check decides divisibility; larger batches take integer
 // remainders.
-__device__ __forceinline__ void admissible_counts(const EstimateArgs& A, int Bg, int tid, int wid, int lane,
+__device__ __forceinline__ void admissible_counts(const EstimateArgs& A, int Bg, int top, int tid, int wid, int lane,
                                                   unsigned long long* group_ok, int (&mm)[kMaxDp / 256])
 {
     const bool small_batch = Bg < (1 << 20);
@@ -1741,7 +1743,8 @@ __device__ __forceinline__ void admissible_counts(const EstimateArgs& A, int Bg,
     for (int h = 0; h < kMaxDp / 256; ++h) {
         const int dp = h * 256 + tid + 1;
         mm[h] = 0;
-        if (small_batch) {
+        const bool in = dp <= top;
+        if (in && small_batch) {
             const int q = (int)rintf((float)Bg * __builtin_amdgcn_rcpf((float)dp));
             if (q * dp == Bg) {
                 for (int i = 0; i < A.n_m; ++i) {
@@ -1750,7 +1753,7 @@ __device__ __forceinline__ void admissible_counts(const EstimateArgs& A, int Bg,
                     if (r * m == q) mm[h] = m > mm[h] ? m : mm[h];
                 }
             }
-        } else {
+        } else if (in) {
             for (int i = 0; i < A.n_m; ++i)
                 if (Bg % (dp * A.m_values[i]) == 0) mm[h] = A.m_values[i] > mm[h] ? A.m_values[i] : mm[h];
         }
@@ -1839,7 +1842,7 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
     }
     if (tid < kLmax + 4) B.wanted[tid] = 0;
     int mm[kMaxDp / 256];
-    admissible_counts(A, jb.Bg, tid, wid, lane, B.group_ok, mm);
+    admissible_counts(A, jb.Bg, B.cnt_n[part], tid, wid, lane, B.group_ok, mm);
     jb.moe = __syncthreads_or(has_q) != 0;
     if (wid == 0 || wid == 1) {
         const float* src = (wid == 0 ? A.p : A.a) + off;
@@ -1899,8 +1902,13 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         return __umul24(pp, grp) == (unsigned)n && pp <= jb.L ? pp : 0;
     };
     // the degrees some count of the item requests: a lane per pair, a wave per
-    // fourth count
-    for (int e = lane; e < n_pairs; e += 64) {
+    // fourth count.  A batch with many divisors over many counts takes every degree
+    // instead: the tests would cost more than the recursion's extra rows (512
+    // trace-like jobs x 8 types x counts 1 .. 255: batches of 55,440, 1374 us with the
+    // tests and 1345 without, of 720,720, 1196 and 1070; over 32 counts, 133 and 137)
+    if (n_pairs * part_counts(A, part) > kWantedTests) {
+        if (tid < jb.L) B.wanted[tid + 1] = 1;
+    } else for (int e = lane; e < n_pairs; e += 64) {
         const int ti = (int)(((float)e + 0.5f) * r_dps);
         const int grp = (int)B.tps[ti] * (int)(B.dps[e - ti * n_dps] & 0xFFFFu);
         const float r_grp = __builtin_amdgcn_rcpf((float)grp);
@@ -2600,7 +2608,7 @@ __device__ __forceinline__ void estimate_tab_body(const EstimateArgs& A, int wid
         B.q[tid] = A.q[off + tid];
     }
     int mm[kMaxDp / 256];
-    admissible_counts(A, jb.Bg, tid, wid, lane, B.group_ok, mm);
+    admissible_counts(A, jb.Bg, B.cnt_n[part], tid, wid, lane, B.group_ok, mm);
     if (tid < A.n_m) B.mval[tid] = (uint8_t)A.m_values[tid];
     if (tid < 2 * K) {
         const int link = tid / K, k = tid - link * K;

@@ -191,6 +191,38 @@ def test_many_targets_per_cell(oracle, rule, shared):
     assert cnt["plans"] + cnt["plans_skipped"] == size["plans"] and 0 < rep["infeasible"] < len(ids)
 
 
+def test_dense_counts_of_a_divisor_rich_batch(oracle):
+    """A batch with many divisors over every count up to 255: the set-up takes every
+    degree without looking which are requested (a block per item, many counts), and the
+    cells are bitwise those of a third of the counts at a time, where it looks."""
+    rng = np.random.default_rng(12)
+    L, batch = 40, 720720
+    job = lambda: dict(t=list(rng.lognormal(-5, 0.6, L)), p=list(rng.uniform(1e8, 4e8, L)),
+                       a=list(rng.uniform(2e4, 6e4, L)), x=list(rng.uniform(1e3, 4e3, L)), a2a=[0.0] * L, batch=batch)
+    types = [dict(speed=1.0, mem=12e9, bw_intra=300e9, bw_inter=25e9, gpus_per_node=8),
+             dict(speed=0.6, mem=40e9, bw_intra=64e9, bw_inter=12.5e9, gpus_per_node=12)]
+    jobs = [job() for _ in range(4)] * 64                 # 512 items: a block each
+    counts = np.arange(1, 256)
+    degrees = [d for d in range(1, 256) if batch % d == 0]
+    tests = [len(degrees) * sum(1 for tp in range(1, 13) if g % tp == 0) * len(counts) for g in (8, 12)]
+    assert min(tests) > 1 << 16 and max(tests) / 3 < 1 << 16
+    kappa = rng.uniform(1.0, 2.0, (len(types), len(counts)))
+    w = wl.from_lists(jobs, types, counts, [1, 2], kappa=kappa.ravel())
+    res, cnt, size = _run(w)
+    _say(f"divisor-rich batch: {w.n_cells} cells, {size['max_plans_per_cell']} plans per cell")
+    grid = lambda v, n: v.reshape(len(jobs), len(types), n, -1)
+    for third in range(3):
+        sub = counts[third::3]
+        part, _, _ = _run(wl.from_lists(jobs, types, sub, [1, 2], kappa=kappa[:, third::3].ravel()))
+        for k in ("t_iter", "thr", "plan", "cuts"):
+            assert np.array_equal(grid(res[k], len(counts))[:, :, third::3], grid(part[k], len(sub))), (third, k)
+    ids = np.arange(0, 4 * len(types) * len(counts), 5)
+    full = {k: v[ids] for k, v in res.items()}
+    rep = compare(w, full, ids, oracle)
+    _check(rep, "divisor-rich batch")
+    assert cnt["plans"] + cnt["plans_skipped"] == size["plans"]
+
+
 GOLDEN = json.load(open(os.path.join(HERE, "golden", "cells_hand.json")))
 
 
