@@ -877,6 +877,29 @@ int estimate_parts(const arena_ctx* c, int64_t blocks)
     return (int)std::max<int64_t>(1, std::min({most, (deep ? 4 : 2) * cus / items, blocks / items}));
 }
 
+// Counts of a block from which a type with one contention factor may keep its
+// problems' bottlenecks for all of them.  256 jobs x 4 types x 35 counts: 64 layers,
+// 507 us without and 359 with; mixture of experts, 822 and 806; trace-like, 306 and
+// 314.  With fewer the sample cells are most of the cells (32 jobs of 128 layers x 8
+// types x 52 counts, 26 a block: 382 and 527).  Under the memory rule, whose pricing
+// outweighs its recursions, from twice as many (128 trace-like jobs x 4 types x 35
+// counts: 455 and 495; 128 mixed jobs x 8 types x 131 counts: 5057 and 4199).
+constexpr int kShareCounts = 32;
+
+// Whether some type has one contention factor for all its counts, and a block
+// enough counts (the kernel itself looks which types, so a captured call stays
+// right when the factors change).
+bool shares_bottlenecks(const arena_ctx* c, int parts)
+{
+    const bool mem = c->partition_rule == ARENA_PARTITION_MEMORY;
+    if (c->n_counts / parts < (mem ? 2 : 1) * kShareCounts) return false;
+    for (int g = 0; g < c->n_types; ++g) {
+        const float* k = c->kappa.data() + (size_t)g * c->n_counts;
+        if (std::all_of(k, k + c->n_counts, [k](float v) { return v == k[0]; })) return true;
+    }
+    return false;
+}
+
 // Kernel arguments from the context, with the library-owned tables at the
 // given device addresses.
 arena::EstimateArgs estimate_args(const arena_ctx* c, const int32_t* d_off, const int32_t* d_batch,
@@ -903,6 +926,7 @@ arena::EstimateArgs estimate_args(const arena_ctx* c, const int32_t* d_off, cons
     A.n_items = c->n_jobs * c->n_types;
     // one block per resident slot (four per CU); each takes items from the queue
     A.n_parts = parts;
+    A.share = shares_bottlenecks(c, parts) ? 1 : 0;
     A.n_blocks = estimate_blocks(c, parts);
     A.pure_cuts = d_pcut;
     // ascending: the kernel bisects the microbatch counts for the memory limit

@@ -58,6 +58,7 @@ struct EstimateArgs {
     uint8_t* pure_cuts;           // [n_blocks * kPureCutBytes] each block's cache of pure-compute splits
     const int32_t* count_order;   // [NC] count indices, largest count first
     int32_t n_jobs, n_types, n_counts;
+    int32_t share;                // some type has one contention factor for all its counts, and they are many
     int32_t n_m;
     int32_t m_values[kMaxM];
     double tie_eps;

@@ -20,7 +20,12 @@
 // counts) solving every tensor degree's problem for every requested degree at
 // set-up, to share over the counts, took 6.07 ms; certifying a bottleneck when
 // a plan needs one takes 3.66 ms (3.54 ms when those are kept for the other
-// counts, but then the work done depends on which wave comes first).
+// counts, but then the work done depends on which wave comes first).  Over many
+// counts that loses to the set-up (64 jobs x 8 types x 131 counts: 1036 us then,
+// 2003 with certificates and recursions in every cell), so there a sample of the
+// cells decides it per item: 881 us; 256 lognormal jobs of 64 layers x 4 types x 35
+// counts 428, 507 and 359; trace-like jobs, which seldom need a recursion, 410, 306
+// and 314.
 // Nothing here is a dense contraction, so no MFMA: the work is compares,
 // min/max and adds on the vector ALU; reductions use DPP row operations.
 //
@@ -44,7 +49,7 @@ constexpr int kPad = 8;            // prefix arrays hold +inf past the last laye
 constexpr int kLevels = 7;         // successor tables: 2^7 > largest stage count - 1
 constexpr int kLevelStride = 132;  // bytes per successor table (>= kLmax + 1)
 constexpr int kMaxTp = 8;          // tensor degrees of one type (divisors of a node size <= 31)
-constexpr int kMaxDps = 240;       // data-parallel degrees of one job: divisors <= 1024 of a batch below
+constexpr int kMaxDps = 234;       // data-parallel degrees of one job: divisors <= 1024 of a batch below
                                    // 2^31 (233 at most, for 1,396,755,360), no larger than the largest count
 constexpr int kTargets = 64;       // plans' (pp, tp, dp) a wave bounds and orders at a time
 constexpr int kWantedTests = 1 << 16;  // (pair, count) tests at set-up up to which the requested degrees are looked for
@@ -61,7 +66,7 @@ struct WaveLds {
     double planT[kMaxPlans];      // iteration time of each plan of the cell (+inf: does not fit)
     uint32_t planKey[kMaxPlans];  // pp << 12 | tp << 7 | m
     double bq[kMaxM];             // samples per microbatch of the admissible counts, ascending m
-    int32_t mq[kMaxM];            // those microbatch counts
+    uint8_t mq[kMaxM];            // those microbatch counts (<= 127)
     union {
         struct {
             uint32_t tkey[kTargets];  // the cell's targets (target_key) and lower bounds of their plans' times,
@@ -91,7 +96,11 @@ struct BlockLds {
     double Wpure[kLmax + 1];      // its bottleneck, by degree (the degrees some count requests)
     uint32_t dps[kMaxDps];        // data-parallel degrees some listed m admits, largest first: dp, and the
                                   // largest m with dp m dividing the batch from bit 16
-    unsigned long long group_ok[kMaxDp / 64];   // set-up: the admitted degrees, 64 candidates per ballot
+    union {
+        unsigned long long group_ok[kMaxDp / 64];   // set-up: the admitted degrees, 64 candidates per ballot
+        uint16_t bneck[kMaxTp][kLmax];   // SHARE: [tensor degree][degree - 1]: the layers [c, e) (c, and e from
+                                  //   bit 8) whose cost is the bottleneck
+    };
     double p_layer_max;           // largest parameter bytes of one layer
     double x_layer_min;           // smallest boundary activation bytes of one layer
     double x_sum, q_sum;          // sums over the layers of x and of the all-to-all bytes
@@ -99,12 +108,15 @@ struct BlockLds {
     double head_a[kHeadLayers];   //   differences (0 past the layer count)
     float xwin[kLmax + 1];        // [pp]: least x bytes of a window of layers whose pure-compute cost
     float qwin[kLmax + 1];        //   reaches Wpure[pp], and least all-to-all bytes (rounded down)
-    uint8_t wanted[kLmax + 4];    // [pp]: some count of the item requests the degree
+    alignas(4) uint8_t wanted[kLmax + 4];    // [pp]: some count of the item requests the degree (SHARE: bit i,
+                                  //   with tensor degree tps[i])
     uint8_t tps[kMaxTp];          // the node size's divisors
     uint16_t cnt_n[kMaxCounts];   // GPU counts, largest first, and their indices; kept for the whole launch
     uint16_t cnt_i[kMaxCounts];
     int32_t n_tps, n_dps;
     int32_t next_cell;
+    int32_t share;                // SHARE: one contention factor for all counts of the type
+    uint32_t asked;               // SHARE: a sample cell has had to solve a problem
     unsigned long long pure_cached[2];   // bit pp-1: the block's cache row of the pure split of pp is current
     WaveLds w[kWavesPerBlock];
 };
@@ -1794,10 +1806,40 @@ __device__ __forceinline__ int part_counts(const EstimateArgs& A, int part)
     return (A.n_counts - part + A.n_parts - 1) / A.n_parts;
 }
 
+// The bottleneck of degree pp of tensor degree tps[ti]'s problem, whose layer
+// costs are the prefix in the wave's UD, from the item's shared table.  Every
+// bottleneck is the cost of some run of layers (the recursion only forms
+// differences of the prefix and picks among them), so the table keeps that run,
+// two bytes, and the difference gives the same double again.
+__device__ __forceinline__ double shared_bottleneck(const BlockLds& B, const WaveLds& Wv, int ti, int pp)
+{
+    const int run = B.bneck[ti][pp - 1];
+    return Wv.UD[2 * (run >> 8)] - Wv.UD[2 * (run & 255)];
+}
+
+// Solves the problem in the wave's UD (tensor degree tps[ti]) for the degrees in
+// tm into the item's shared table.
+__device__ void solve_shared(BlockLds& B, WaveLds& Wv, int lane, int L, int ti, Mask tm)
+{
+    solve_dp(Wv, L, tm, lane, [&](int pp, double W, Mask m) -> Mask {
+        // the run that costs W: the longest one ending at e within W, for the first e where it costs just W
+        successor_tables<2>(Wv.UD, Wv.J, lane, L, 1, W);
+        const int e0 = 1 + lane, e1 = 65 + lane;
+        const bool h0 = e0 <= L && Wv.UD[2 * e0] - Wv.UD[2 * Wv.J[e0]] == W;
+        const bool h1 = e1 <= L && Wv.UD[2 * e1] - Wv.UD[2 * Wv.J[e1 <= L ? e1 : 0]] == W;
+        const unsigned long long b0 = __ballot(h0), b1 = __ballot(h1);
+        const int e = b0 ? 1 + (int)__builtin_ctzll(b0) : 65 + (int)__builtin_ctzll(b1 | (1ull << 63));
+        if (lane == 0) B.bneck[ti][pp - 1] = (uint16_t)(Wv.J[e] | (e << 8));
+        wave_sync();
+        return m;
+    });
+}
+
 // MEM: the memory-constrained partition rule (each wave has one more LDS
 // row for its recursion); EXT: the exact-T rule (that row holds its
-// suffix recursion).
-template <bool MEM, bool EXT = false>
+// suffix recursion); SHARE: types with one contention factor for all counts may
+// keep their problems' bottlenecks for all counts of the item.
+template <bool MEM, bool EXT = false, bool SHARE = false>
 __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, int item, int part = 0)
 {
     __shared__ BlockLds B;
@@ -1871,7 +1913,13 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         const bool td = lane < 32 && ((ty.divs >> lane) & 1u);
         const unsigned tdm = (unsigned)__ballot(td);
         if (td) B.tps[__popc(tdm & ((1u << lane) - 1u))] = (uint8_t)lane;
+        bool same = true;
+        if (SHARE)
+            for (int c = lane; c < A.n_counts; c += 64) same &= A.kappa[g * A.n_counts + c] == A.kappa[g * A.n_counts];
+        const bool uniform = SHARE && __ballot(!same) == 0ull && part_counts(A, part) >= 2 * kWavesPerBlock;
         if (lane == 0) {
+            B.share = uniform ? 1 : 0;
+            B.asked = 0u;
             B.n_tps = __popc(tdm);
             B.x_sum = xs;
             B.q_sum = qs;
@@ -1907,7 +1955,7 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
     // trace-like jobs x 8 types x counts 1 .. 255: batches of 55,440, 1374 us with the
     // tests and 1345 without, of 720,720, 1196 and 1070; over 32 counts, 133 and 137)
     if (n_pairs * part_counts(A, part) > kWantedTests) {
-        if (tid < jb.L) B.wanted[tid + 1] = 1;
+        if (tid < jb.L) B.wanted[tid + 1] = 0xFF;
     } else for (int e = lane; e < n_pairs; e += 64) {
         const int ti = (int)(((float)e + 0.5f) * r_dps);
         const int grp = (int)B.tps[ti] * (int)(B.dps[e - ti * n_dps] & 0xFFFFu);
@@ -1915,7 +1963,10 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
         for (int c = part + A.n_parts * wid; c < A.n_counts; c += A.n_parts * kWavesPerBlock) {
             const int n = B.cnt_n[c];
             const int pp = (int)rintf((float)n * r_grp);
-            if (__umul24(pp, grp) == (unsigned)n && pp <= jb.L) B.wanted[pp] = 1;
+            if (__umul24(pp, grp) == (unsigned)n && pp <= jb.L) {
+                if constexpr (SHARE) atomicOr((unsigned*)B.wanted + (pp >> 2), 1u << (8 * (pp & 3) + ti));
+                else B.wanted[pp] = 1;
+            }
         }
     }
     if (wid == 0) tally(Wv, lane, kCells, (unsigned long long)part_counts(A, part));
@@ -1939,15 +1990,57 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
     window_minima(B, Wv, lane, wid, jb.L, wanted, A.x + off, A.q + off, jb.moe);
     __syncthreads();
 
+    const bool share = SHARE && __builtin_amdgcn_readfirstlane((int)B.share) != 0;
+    const int stride = part_counts(A, part) / kWavesPerBlock;   // between the sample cells
+    unsigned shared = 0u;         // bit i: tensor degree tps[i]'s bottlenecks are in the item's table (bneck)
+
     // ---- cells: take counts, largest first, from the block's work counter
-    for (;;) {
+    for (int turn = 0;; ++turn) {
         // the lane index is re-derived per cell, for the same reason as the
         // thread index per item
         int lane;
         __asm__ volatile("" : "=v"(lane) : "0"((int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u))));
+        if (share && turn == 1) {
+            // With one contention factor a problem does not depend on the count.  A sample
+            // of the cells, one a wave, shows whether certificates do: if any of them had
+            // to solve a problem, every problem is solved here, for all degrees that some
+            // count requests and the memory bound of target_bound (same margin and more)
+            // leaves, and the other cells read the bottlenecks.  The waves take the tensor
+            // degrees in turn, by index: control flow here must not hang on a lane (a
+            // queue's lane-0 atomic next to the tally's lane-0 branch is threaded into a
+            // loop that the other lanes go round by themselves).
+            __syncthreads();
+            const int first = jb.moe ? 0 : 1, n_tps = __builtin_amdgcn_readfirstlane(B.n_tps);
+            if (__builtin_amdgcn_readfirstlane((int)B.asked)) shared = ((1u << n_tps) - 1u) & ~((1u << first) - 1u);
+            for (int ti = first + wid; shared && ti < n_tps; ti += kWavesPerBlock) {
+                const int tp = __builtin_amdgcn_readfirstlane((int)B.tps[ti]);
+                const double cap = ty.mem * (double)tp * (1.0 + 2e-9), Pall = B.Pp[jb.L];
+                auto may = [&](int pp) {
+                    if (!((B.wanted[pp] >> ti) & 1)) return false;
+                    return !A.prune || 4.0 * fmax(Pall / (double)pp, B.p_layer_max) <= cap;
+                };
+                const Mask tm = ballot_mask(may(1 + lane), may(65 + lane));
+                if (!tm.any()) continue;
+                build_prefix_u<2>(B.t, B.x, B.q, Wv.UD, Wv.UD + 1, lane, jb, ty, (double)A.kappa[g * A.n_counts], tp, true);
+                solve_shared(B, Wv, lane, jb.L, ti, tm);
+                tally(Wv, lane, kProblems, 1);
+                tally(Wv, lane, kAlgOps, 8ull * (unsigned)jb.L);
+            }
+            __syncthreads();
+        }
         int cix = 0;
-        if (lane == 0) cix = atomicAdd(&B.next_cell, 1);
-        cix = __builtin_amdgcn_readfirstlane(cix) * A.n_parts + part;
+        if (share && turn == 0) {
+            cix = wid * stride;
+        } else {
+            if (lane == 0) cix = atomicAdd(&B.next_cell, 1);
+            cix = __builtin_amdgcn_readfirstlane(cix);
+            // the others lie between and behind the samples
+            if (share) {
+                const int before = cix / (stride - 1);
+                cix += before < kWavesPerBlock ? before + 1 : kWavesPerBlock;
+            }
+        }
+        cix = cix * A.n_parts + part;
         if (cix >= A.n_counts) break;
         const int ci = B.cnt_i[cix];
         Cell cell;
@@ -2056,7 +2149,9 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
                     // a certificate, unless the recursion passes the degree's row anyway
                     // (not under the exact-T rule, whose pricing outweighs its few
                     // recursions)
-                    if (!EXT && pc >= kCertMinDegree && pc > deepest) {
+                    if (SHARE && ((shared >> __popc(ty.divs & ((1u << tp0) - 1u))) & 1u)) {
+                        wc = shared_bottleneck(B, Wv, __popc(ty.divs & ((1u << tp0) - 1u)), pc);
+                    } else if (!EXT && pc >= kCertMinDegree && pc > deepest) {
                         const Stages sp = pure_split(B.Upure, B.Wpure[pc], B.pure_cached, Wv, pcache, lane, jb.L, pc);
                         if constexpr (MEM) {
                             wc = certified_bottleneck<2>(sp, Wv, lane, jb.L, pc);
@@ -2088,6 +2183,7 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
                 }
                 open = within(open);
                 if (!open) continue;
+                if (share && turn == 0 && lane == 0) B.asked = 1u;
                 // the degrees still wanted, one mask bit each
                 auto degrees = [&](unsigned long long of) -> Mask {
                     Mask dm{0ull, 0ull};
@@ -2171,11 +2267,14 @@ __device__ __forceinline__ void estimate_body(const EstimateArgs& A, int wid, in
                 W = B.Wpure[pp];
             } else {
                 build_prefix_u<2>(B.t, B.x, B.q, Wv.UD, Wv.UD + 1, lane, jb, ty, cell.kappa, tp, true);
+                const int ti = __popc(ty.divs & ((1u << tp) - 1u));
+                const bool known = SHARE && ((shared >> ti) & 1u);
+                if (known) W = shared_bottleneck(B, Wv, ti, pp);
                 Mask one;
                 one.lo = pp <= 64 ? (1ull << (pp - 1)) : 0ull;
                 one.hi = pp > 64 ? (1ull << (pp - 65)) : 0ull;
                 const unsigned long long e0 = Wv.tally[kDpEntries];   // the cuts' rerun is not tallied
-                solve_dp(Wv, jb.L, one, lane, [&](int, double Wk, Mask mk) {
+                if (!known) solve_dp(Wv, jb.L, one, lane, [&](int, double Wk, Mask mk) {
                     W = Wk;
                     return mk;
                 });
@@ -2262,17 +2361,18 @@ __device__ __forceinline__ int take_item(const EstimateArgs& A, int* slot, int w
     return item;
 }
 
+template <bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_kernel(EstimateArgs A)
 {
     __shared__ int slot[2];
     int part;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    estimate_body<false>(A, wid, kZeroTallies);
+    estimate_body<false, false, SHARE>(A, wid, kZeroTallies);
     for (int item = take_item(A, slot, wid, part); item >= 0; item = take_item(A, slot, wid, part)) {
-        estimate_body<false>(A, wid, item, part);
+        estimate_body<false, false, SHARE>(A, wid, item, part);
         __syncthreads();
     }
-    estimate_body<false>(A, wid, kFlushTallies);
+    estimate_body<false, false, SHARE>(A, wid, kFlushTallies);
 }
 
 // The exact-T rule: each plan's split minimises its iteration time.
@@ -2293,17 +2393,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // aims at four waves per SIMD (its recursion row shares LDS with the cut
 // tables, so four blocks fit a CU) and spills the rest, which measured faster
 // than three or two waves with fewer spills.
+template <bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void estimate_mem_kernel(EstimateArgs A)
 {
     __shared__ int slot[2];
     int part;
     const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    estimate_body<true>(A, wid, kZeroTallies);
+    estimate_body<true, false, SHARE>(A, wid, kZeroTallies);
     for (int item = take_item(A, slot, wid, part); item >= 0; item = take_item(A, slot, wid, part)) {
-        estimate_body<true>(A, wid, item, part);
+        estimate_body<true, false, SHARE>(A, wid, item, part);
         __syncthreads();
     }
-    estimate_body<true>(A, wid, kFlushTallies);
+    estimate_body<true, false, SHARE>(A, wid, kFlushTallies);
 }
 
 // ------------------------------------------------------------ interpolated communication latency
@@ -3002,9 +3103,11 @@ hipError_t launch_estimate(const EstimateArgs& args, hipStream_t stream)
     } else if (args.exact_t) {
         hipLaunchKernelGGL(estimate_ext_kernel, grid, block, 0, stream, args);
     } else if (args.mem_rule) {
-        hipLaunchKernelGGL(estimate_mem_kernel, grid, block, 0, stream, args);
+        if (args.share) hipLaunchKernelGGL((estimate_mem_kernel<true>), grid, block, 0, stream, args);
+        else hipLaunchKernelGGL((estimate_mem_kernel<false>), grid, block, 0, stream, args);
     } else {
-        hipLaunchKernelGGL(estimate_kernel, grid, block, 0, stream, args);
+        if (args.share) hipLaunchKernelGGL((estimate_kernel<true>), grid, block, 0, stream, args);
+        else hipLaunchKernelGGL((estimate_kernel<false>), grid, block, 0, stream, args);
     }
     return hipGetLastError();
 }

@@ -191,6 +191,66 @@ def test_many_targets_per_cell(oracle, rule, shared):
     assert cnt["plans"] + cnt["plans_skipped"] == size["plans"] and 0 < rep["infeasible"] < len(ids)
 
 
+@pytest.mark.parametrize("rule", [arena.PARTITION_BALANCED, arena.PARTITION_MEMORY])
+@pytest.mark.parametrize("kind", ["uniform", "trace", "moe"])
+def test_bottlenecks_shared_over_many_counts(oracle, kind, rule):
+    """Types with one contention factor over many counts keep their bottlenecks for all
+    counts of an item when a sample of the cells had to solve a problem: every cell and
+    cut row is bitwise that of the counts in groups too small for it, with pruning and
+    without, a type with a factor per count beside them; the tallies do not depend on
+    the run, and a sample of cells agrees with the oracle."""
+    import dataclasses
+    # 540 items: a block each; half of the counts are too few
+    top = 38 if rule == arena.PARTITION_BALANCED else 70
+    n_jobs, counts = 180, np.asarray([1, 2, 4] + list(range(8, 8 * top + 1, 8)))
+    if kind == "uniform":
+        rng = np.random.default_rng(15)
+        job = lambda L: dict(t=list(rng.uniform(1e-3, 5e-3, L)), p=list(rng.uniform(5e7, 1.5e8, L)),
+                             a=list(rng.uniform(2e7, 6e7, L)), x=list(rng.uniform(1e6, 4e6, L)), a2a=[0.0] * L, batch=256)
+        types = [dict(speed=1.0, mem=96e9, bw_intra=300e9, bw_inter=25e9, gpus_per_node=8),
+                 dict(speed=0.7, mem=30e9, bw_intra=64e9, bw_inter=12.5e9, gpus_per_node=12),
+                 dict(speed=0.4, mem=24e9, bw_intra=32e9, bw_inter=12.5e9, gpus_per_node=4)]
+        w = wl.from_lists([job(int(L)) for L in np.linspace(1, 128, n_jobs)], types, counts, [1, 2, 4, 8, 16])
+    else:
+        base = wl.trace(n_jobs=n_jobs) if kind == "trace" else wl.moe(n_jobs=n_jobs)
+        w = dataclasses.replace(base, counts=counts.astype(np.int32), speed=base.speed[:3], mem=base.mem[:3],
+                                bw_intra=base.bw_intra[:3], bw_inter=base.bw_inter[:3],
+                                gpus_per_node=base.gpus_per_node[:3], hbm=None if base.hbm is None else base.hbm[:3])
+    rng = np.random.default_rng(16)
+    kappa = np.repeat(np.asarray([[1.0], [1.5], [1.0]]), len(counts), axis=1)
+    kappa[2] = rng.uniform(1.0, 2.0, len(counts))
+    with_counts = lambda pick: dataclasses.replace(
+        w, counts=counts[pick].astype(np.int32),
+        kappa=np.ascontiguousarray(kappa[:, pick].reshape(1, -1).astype(np.float32)))
+
+    def run(v, prune=True):
+        est = arena.Estimator(v, with_cuts=True, prune=prune, rule=rule)
+        try:
+            est.estimate()
+            return est.results(), est.counters(), est.space_size()
+        finally:
+            est.close()
+
+    every = with_counts(np.arange(len(counts)))
+    res, cnt, size = run(every)
+    again, cnt2, _ = run(every)
+    full, cntf, _ = run(every, prune=False)
+    _say(f"shared bottlenecks: {kind} rule {rule}: {every.n_cells} cells, {cnt['problems']} problems, "
+         f"{cntf['problems']} without pruning")
+    assert cnt == cnt2 and cntf["plans"] == size["plans"]
+    grid = lambda v, n: v.reshape(n_jobs, 3, n, -1)
+    for k in ("t_iter", "thr", "plan", "cuts"):
+        assert np.array_equal(res[k], again[k]) and np.array_equal(res[k], full[k]), k
+    for s in range(2):
+        pick = np.arange(s, len(counts), 2)
+        part, _, _ = run(with_counts(pick))
+        for k in ("t_iter", "thr", "plan", "cuts"):
+            assert np.array_equal(grid(res[k], len(counts))[:, :, s::2], grid(part[k], len(pick))), (s, k)
+    ids = np.arange(0, every.n_cells, 97 if rule == arena.PARTITION_BALANCED else 797)
+    rep = compare(every, {k: v[ids] for k, v in res.items()}, ids, oracle, rule=rule)
+    _check(rep, "shared bottlenecks")
+
+
 def test_dense_counts_of_a_divisor_rich_batch(oracle):
     """A batch with many divisors over every count up to 255: the set-up takes every
     degree without looking which are requested (a block per item, many counts), and the
