@@ -9,38 +9,40 @@
 // whose rho after its scale-down is least, and the worst-off job moved to
 // its least-rho count.  The step is a chain of dependent decisions,
 // each an arg-min over the running jobs or over one job's grids, so one
-// workgroup runs the whole step and each decision is a block-wide reduction
-// of (key, index) pairs -- index breaking ties -- over per-thread candidates.
+// workgroup runs the whole step.  Costs and gains are float64 from the float32
+// matrix, in the same operation order as a plain evaluation, and indices break
+// ties, so every decision is reproducible.
 //
-// The step is latency-bound (one small decision after another), so the
-// design removes latency from each decision:
-//  * the running jobs are compacted into an LDS list at the start, with each
-//    one's allocation and best scale-down (cost, count, type) cached beside
-//    it: a move changes one job, so only its entry is recomputed, and a
-//    scale-down search is one pass over LDS;
-//  * the next queued job's throughput row is loaded while the current job is
-//    visited (all loads of a thread in flight together) and staged in LDS,
-//    so every launch decision reads LDS;
-//  * a decision reduces within each wave by DPP row rotations (VALU, no LDS
-//    traffic) and read-lanes, and across the 4 waves through a double-
-//    buffered LDS slot: one barrier per decision.
-// The visit of the queue, a chain of a thousand decisions and more, is then one
-// wave's (visit_fast): no decision waits for a barrier or for global memory, and
-// few for more than two dependent LDS reads.
-//  * Other waves, one per ring slot, turn the next queued jobs' rows into the best
-//    throughput and count up to every count of each type, so a launch search is
-//    one read per type and a wave minimum.
+// The step is latency-bound (one small decision after another), so the design
+// removes latency from each decision.
+//
+// The queue is visited by one wave (visit_fast) when a job's row has at most 2048
+// grids and at most 1152 jobs run or queue: no decision waits for a barrier or for
+// global memory, and few for more than two dependent LDS reads.
+//  * Up to seven other waves, one per ring slot, turn the next queued jobs' rows
+//    into the best throughput and count up to every count of each type, so a launch
+//    search is one read per type and a wave minimum.
 //  * A running job's next scale-downs (kLevels of them, each the step after the
-//    one before) sit in LDS from the start, so a move's next cost is a read.
+//    one before) sit in LDS from the start, so a move's next cost is a read and a
+//    scale-down search one pass over LDS.
 // Measured on 16384 jobs x 8 types x 131 counts (748 decisions): 1133 us a step by
 // the whole block, 547 us with the rows prepared and one wave deciding, 381 us with
 // the scale-downs ahead and the searches' reads independent; 1500 jobs of which
 // 900 run, fairness and deadlines (765 decisions): 939 -> 438 us.
-// A row too large for the ring, or more running and queued jobs than the slots,
-// take the visit by the whole block (visit_block).  When more jobs run than its
-// list holds, that one scans every job instead (same decisions, slower).  Costs and gains are float64 from the float32
-// matrix, in the same operation order as a plain evaluation, so every
-// decision is reproducible.
+//
+// A larger row, or more running and queued jobs, take the visit by the whole block
+// (visit_block), and the scale-ups at the end always take the block:
+//  * the running jobs are compacted into an LDS list at the start, with each
+//    one's allocation and best scale-down (cost, count, type) cached beside it: a
+//    move changes one job, so only its entry is recomputed;
+//  * the next queued job's throughput row is loaded while the current job is
+//    visited (all loads of a thread in flight together) and staged in LDS when it
+//    fits;
+//  * a decision reduces within each wave by DPP row rotations (VALU, no LDS
+//    traffic) and read-lanes, and across the 4 waves through a double-
+//    buffered LDS slot: one barrier per decision.
+// When more jobs run than the list holds, the block scans every job instead (same
+// decisions, slower).
 #include <math.h>
 
 #include "arena_internal.h"
