@@ -866,7 +866,10 @@ int cache_blocks(const arena_ctx* c)
 // other).  32 jobs of up to 96 layers x 4 types x 35 counts: 188 us in 128 blocks,
 // 137 in 512, 219 in 1024; 64 jobs of up to 48 layers x 3 types x 7 counts: 67 us
 // in 192 blocks, 95 in 384; 32 jobs of 128 layers x 4 types x 8 counts: 61 us in
-// 128 blocks, 85 in 384.
+// 128 blocks, 85 in 384.  At the lines: 2 jobs x 8 types, uniform layers: 64 counts
+// 257 us for 96 layers and 186 for 97, 63 counts 360 for 128 layers and 250 with one
+// count more (the deeper split would pay before either line; one block per item takes
+// 4 to 7 times as long); tables, 48 jobs x 4 types: 8 counts 1004 us, 9 counts 692.
 int estimate_parts(const arena_ctx* c, int64_t blocks)
 {
     const bool deep = c->partition_rule == ARENA_PARTITION_EXACT_T || (c->tab_k > 0 && c->n_counts > 8) ||
