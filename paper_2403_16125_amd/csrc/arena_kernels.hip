@@ -1079,8 +1079,8 @@ __device__ __forceinline__ bool ext_fits(const ExtCtx& E, const double* Pp, cons
 // prefix: the last one is bisected once and only moves left as t grows (more
 // microbatches in flight), so a row's scan tests nothing but the recursion
 // (testing each end of each row had cost two divisions an end; 512 trace-like
-// jobs x 140 grids, with the thresholds skipped below: 26.0 -> 5.5 ms).  KIND 1 and 2
-// stop where the stage alone reaches the best (it only grows with e).
+// jobs x 140 grids, with the thresholds skipped below: 26.0 -> 5.4-5.7 ms).  KIND 1
+// and 2 stop where the stage alone reaches the best (it only grows with e).
 template <int S, int KIND>
 __device__ double ext_rows(const ExtCtx& E, const double* U, const double* Pp, const double* Ap, const float* x,
                            double* H, int lane, double tS, double tP, int tmax)
@@ -2618,8 +2618,8 @@ __device__ __forceinline__ int tab_b_index(double b)
 // least min(m, pp - l + 1) microbatches of that layer's bytes in flight; f is
 // non-decreasing.  Relative margins of 1e-9 cover reciprocal estimates and the
 // sums' rounding.  1024 jobs x 8 types x 131 counts: 45.0 ms when the wave took one
-// plan after another and summed the layers' costs per (tp, b) of every cell, 18.9
-// ms with the sums tabulated per item and Wpure in the bound.
+// plan after another and summed the layers' costs per (tp, b) of every cell,
+// 19.6-20.7 ms (over seeds) with the sums tabulated per item and Wpure in the bound.
 __device__ __forceinline__ double tab_bound(const TabBlockLds& B, const JobCtx& jb, const TypeDev& ty, int K,
                                             const Cell& cell, unsigned key)
 {
